@@ -212,10 +212,10 @@ cyfa_status cyfa_forward_varlen(const cyfa_fwd_desc *desc,
 
 /*
  * Bytes of device workspace cyfa_backward needs for `desc` (host-only).  The
- * vector-ALU backward keeps the states entering every 16-token chunk and the
- * adjoint states at every chunk's end (2 x B H ceil(T/16) 128 (d_k + d_v)
- * floats) and two 128-float rows per token and head: about 4.6 GB at B=4,
- * T=4096, H=16, d=128.  The matrix-core backward keeps each chunk group's state
+ * fp32 backward keeps the states entering every 64-token chunk and the adjoint
+ * states at every chunk's end (2 x B H ceil(T/64) 128 (d_k + d_v) floats) and
+ * three 128-float rows per token and head: about 1.5 GB at B=4, T=4096, H=16,
+ * d=128.  The bf16 matrix-core backward keeps each chunk group's state
  * contributions and two bf16 128-element rows per token and head: about 0.23 GB
  * there.
  */
@@ -232,11 +232,11 @@ cyfa_status cyfa_backward_workspace_size(const cyfa_fwd_desc *desc, size_t *byte
  * inside the call (only the inputs are needed).
  *
  * desc       as for cyfa_forward: d_k, d_v in {64, 128}, or both 256; m <= 127;
- *            dtype F32 or BF16; segments = chunk groups per sequence for the
- *            parallel kernels (0 = automatic).  kernel MFMA: the matrix-core
- *            backward (BF16 with d_k = d_v = 128; chunk 0 or 32), the automatic
- *            choice there unless chunk is 16; VALU: the vector-ALU backward (chunk
- *            0 or 16; fp32 arithmetic)
+ *            dtype F32 or BF16.  kernel MFMA: the matrix-core backward on bf16
+ *            operands (BF16 with d_k = d_v = 128; chunk 0 or 32; segments = chunk
+ *            groups per sequence, 0 = automatic), the automatic choice there unless
+ *            chunk is 16; VALU: the fp32 backward (chunk 0 or 16, segments 0..1024:
+ *            accepted, and without effect on it)
  * q .. lens, K0, V0, clock0   the forward's inputs, same layouts and NULL rules
  * d_o        [B, T, H, d_v] dtype: dL/do (required)
  * dK_T, dV_T [B, H, 128, d_k] / [B, H, 128, d_v] float: dL/dK_out, dL/dV_out,
@@ -252,7 +252,8 @@ cyfa_status cyfa_backward_workspace_size(const cyfa_fwd_desc *desc, size_t *byte
  * Rows t >= lens[b] of every per-token gradient are written as 0.  Gradients
  * are written, not accumulated.  Outputs must not alias inputs or each other.
  * workspace  at least cyfa_backward_workspace_size bytes, 256-byte aligned.
- * The vector-ALU backward computes in fp32; the matrix-core one multiplies bf16
+ * The fp32 backward computes in fp32 (on the fp32 matrix instructions); the
+ * matrix-core one multiplies bf16
  * operands with fp32 accumulation (states, adjoints and reductions in fp32).  bf16
  * gradients are rounded to nearest even.
  */

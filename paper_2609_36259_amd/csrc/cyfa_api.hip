@@ -194,8 +194,7 @@ cyfa_status plan_backward(const cyfa_fwd_desc *d, BwdPlan *plan) {
     if (d->segments < 0 || d->segments > 1024)
         return fail(CYFA_ERR_INVALID_ARGUMENT, "segments must be in [0, 1024]");
     const int nc = (d->T + chunk - 1) / chunk;
-    int g = d->segments ? d->segments
-                        : (mfma ? cyfa::bwd_mfma_auto_groups(d->B, d->T, d->H) : cyfa::bwd_auto_groups(d->B, d->T, d->H));
+    int g = mfma ? (d->segments ? d->segments : cyfa::bwd_mfma_auto_groups(d->B, d->T, d->H)) : 1;
     if (g > nc) g = nc;
     if (g < 1) g = 1;
     const int cpg = nc > 0 ? (nc + g - 1) / g : 1;
@@ -203,7 +202,7 @@ cyfa_status plan_backward(const cyfa_fwd_desc *d, BwdPlan *plan) {
     plan->mfma = mfma;
     plan->chunk = chunk;
     plan->ws_bytes = mfma ? cyfa::bwd_mfma_workspace_bytes(d->B, d->T, d->H, plan->groups)
-                          : cyfa::bwd_workspace_bytes(d->B, d->T, d->H, d->d_k, d->d_v, plan->groups);
+                          : cyfa::bwd_f32_workspace_bytes(d->B, d->T, d->H, d->d_k, d->d_v);
     return CYFA_OK;
 }
 
@@ -518,7 +517,7 @@ cyfa_status cyfa_backward(const cyfa_fwd_desc *desc, const void *q, const void *
     p.gdelta = d_delta; p.glog_alpha = d_log_alpha; p.gbeta = d_beta; p.gR = d_R;
     p.gK0 = d_K0; p.gV0 = d_V0; p.gclock0 = d_clock0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = plan.mfma ? cyfa::launch_bwd_mfma(p, workspace, s) : cyfa::launch_bwd_valu(p, workspace, s);
+    hipError_t e = plan.mfma ? cyfa::launch_bwd_mfma(p, workspace, s) : cyfa::launch_bwd_f32(p, workspace, s);
     if (e != hipSuccess) return fail(CYFA_ERR_LAUNCH, "backward launch: %s", hipGetErrorString(e));
     return ok();
 }

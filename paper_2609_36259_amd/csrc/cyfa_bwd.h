@@ -45,10 +45,8 @@ struct BwdParams {
     float *U, *dP;                  // [BH][Tpad][128] readout output u_t and key-pass adjoint dp_t
     float *udu, *dlam, *dG;         // [BH][Tpad] <u_t, du_t>, dL/dlambda_t, dL/dG_t
     float *dMp;                     // [BH][groups][128][128] partial dL/dM
-    float *fin;                     // [BH][8] partial sums of <dK_T, Kbar_T> + <dV_T, Vbar_T>
+    double *fin;                    // [BH][8] partial sums of <dK_T, Kbar_T> + <dV_T, Vbar_T>
 };
-
-size_t bwd_workspace_bytes(int B, int T, int H, int dk, int dv, int groups);
 
 // The forward's chunk groups: the state entering each group of cpg 16-token
 // chunks (d_k, d_v in {64, 128}, m <= 127), from the groups' own contributions
@@ -60,12 +58,13 @@ size_t bwd_workspace_bytes(int B, int T, int H, int dk, int dv, int groups);
 size_t group_states_bytes(int B, int H, int dk, int dv, int groups);
 hipError_t launch_group_states(const FwdParams &f, int groups, int cpg, void *ws, const float **EcK,
                                const float **EcV, const double **Eclk, hipStream_t s);
-int bwd_auto_groups(int B, int T, int H);
-hipError_t launch_bwd_valu(BwdParams p, void *ws, hipStream_t s);
 // The last two kernels of either backward: reverse cumulative sums of p.dG and
 // p.dlam (plus the final-state loss p.fin at the last token) into dlog_alpha,
 // ddelta, dclock0; dR from the partial dM of every (b, h, group) in p.dMp.
-hipError_t launch_bwd_tail(const BwdParams &p, hipStream_t s);
+hipError_t launch_bwd_tail(const BwdParams &p, int parts, hipStream_t s);
+// fp32 backward (d_k, d_v in {64, 128} or both 256; m <= 127): its own chunks of 64 tokens.
+size_t bwd_f32_workspace_bytes(int B, int T, int H, int dk, int dv);
+hipError_t launch_bwd_f32(BwdParams p, void *ws, hipStream_t s);
 
 // Matrix-core backward (bf16, d_k = d_v = 128, m <= 127, 32-token chunks, p.nc and
 // p.Tpad counted in those chunks).

@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(kNT, 1) void readout_kernel(Args a) {
         for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
         if (lane == 0) {
             p.fin[(size_t)bh * kCombBlocks + w] = t;
-            p.fin[(size_t)bh * kCombBlocks + 4 + w] = 0.f;
+            p.fin[(size_t)bh * kCombBlocks + 4 + w] = 0.0;
         }
     }
     // the group's dM in paper column order
@@ -1397,7 +1397,7 @@ size_t bwd_mfma_workspace_bytes(int B, int T, int H, int groups) {
     n += 2 * al(BH * Tpad * 128 * 2);
     n += 3 * al(BH * Tpad * 4);
     n += al(BH * G * 128 * 128 * 4);
-    n += al(BH * kCombBlocks * 4);
+    n += al(BH * kCombBlocks * 8);
     return n;
 }
 
@@ -1420,7 +1420,7 @@ hipError_t launch_bwd_mfma(BwdParams p, void *ws, hipStream_t s) {
     p.dlam = reinterpret_cast<float *>(take(BH * Tpad * 4));
     p.dG = reinterpret_cast<float *>(take(BH * Tpad * 4));
     p.dMp = reinterpret_cast<float *>(take(BH * G * 128 * 128 * 4));
-    p.fin = reinterpret_cast<float *>(take(BH * kCombBlocks * 4));
+    p.fin = reinterpret_cast<double *>(take(BH * kCombBlocks * 8));
     a.p = p;
     hipError_t e = launch_readout_prep(p.H, p.m, p.R, nullptr, Mz, p.scale * 1.4426950408889634f, s);
     if (e != hipSuccess) return e;
@@ -1431,7 +1431,7 @@ hipError_t launch_bwd_mfma(BwdParams p, void *ws, hipStream_t s) {
     hipLaunchKernelGGL(grad_kernel, grp, dim3(kNT8), 0, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_bwd_tail(p, s);
+    return launch_bwd_tail(p, p.B * p.groups, s);
 }
 
 }  // namespace cyfa

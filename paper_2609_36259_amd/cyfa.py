@@ -325,7 +325,7 @@ def backward(q, k, v, delta, log_alpha=None, beta=None, R=None, *, d_o, scale=No
     d_delta, d_log_alpha / d_beta (None when the input is None), d_R (None without
     R) and, with ``want_state_grads``, d_K0, d_V0 [B,H,128,d] and d_clock0 [B,H].
     ``kernel``: KERNEL_AUTO (the matrix-core backward for bf16 with d = 128, else
-    the vector-ALU one), KERNEL_VALU or KERNEL_MFMA.
+    the fp32 one), KERNEL_VALU (fp32) or KERNEL_MFMA.
     """
     B, T, H, dk = q.shape
     dv = v.shape[-1]

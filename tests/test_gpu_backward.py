@@ -201,3 +201,28 @@ def test_full_size_sampled_sequence():
                 else v[b:b + 1, h:h + 1] if k in ("d_K0", "d_V0", "d_clock0") else v)
             for k, v in g.items() if v is not None}
     _compare(pick, ref, TOL_BF16, skip=("d_R",))
+
+
+@pytest.mark.parametrize("B,T,H,d,lens", [
+    (1, 1, 1, 64, None),                      # one token
+    (1, 63, 2, 64, None), (1, 64, 1, 128, None), (2, 65, 1, 64, (65, 31)),   # around one 64-token chunk
+    (1, 129, 1, 256, None),                   # three chunks: the readout's last pair has one
+    (8, 65, 4, 256, (65, 64, 33, 32, 31, 1, 0, 65)),   # 256 workgroups: states walked, not scanned
+])
+def test_f32_chunk_edges(B, T, H, d, lens):
+    """Tile, chunk and chunk-pair edges, and both ways of forming the chunks' states.
+    Bar 1e-4 as everywhere for fp32 (sums of up to 256 products: ~1e-6)."""
+    x = make_forward_inputs(B, T, H, d, d, seed=90 + T, dtype="f32")
+    e = _extras(x, 12)
+    _compare(_run(x, e, lens=None if lens is None else np.array(lens, np.int32)),
+             _oracle(x, e, lens=None if lens is None else np.array(lens, np.int32)), TOL_F32)
+
+
+def test_f32_strong_decay():
+    """Stretches of log alpha = -6 and -40 inside a chunk: decays are differences of
+    prefix sums of up to 2560, which a float sum would give to 1e-4 only."""
+    x = make_forward_inputs(1, 128, 2, 64, 64, seed=97, dtype="f32")
+    x["log_alpha"][:, 10:40] = -6.0
+    x["log_alpha"][:, 64:110] = -40.0
+    e = _extras(x, 13)
+    _compare(_run(x, e), _oracle(x, e), TOL_F32)

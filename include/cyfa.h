@@ -211,13 +211,13 @@ cyfa_status cyfa_forward_varlen(const cyfa_fwd_desc *desc,
                                 void *stream);
 
 /*
- * Bytes of device workspace cyfa_backward needs for `desc` (host-only).  The
- * fp32 backward keeps the states entering every 64-token chunk and the adjoint
- * states at every chunk's end (2 x B H ceil(T/64) 128 (d_k + d_v) floats) and
- * three 128-float rows per token and head: about 1.5 GB at B=4, T=4096, H=16,
- * d=128.  The bf16 matrix-core backward keeps each chunk group's state
- * contributions and two bf16 128-element rows per token and head: about 0.23 GB
- * there.
+ * Bytes of device workspace cyfa_backward needs for `desc` (host-only).  For the
+ * fp32 backward: room for the entering and adjoint states of every 16-token chunk
+ * (2 x B H ceil(T/16) 128 (d_k + d_v) floats) and two 128-float rows per token and
+ * head, about 4.6 GB at B=4, T=4096, H=16, d=128 (of which the 64-token chunks that
+ * it works on fill a third), or what its chunks need where that is more.  The bf16
+ * matrix-core backward keeps each chunk group's state contributions and two bf16
+ * 128-element rows per token and head: about 0.23 GB there.
  */
 cyfa_status cyfa_backward_workspace_size(const cyfa_fwd_desc *desc, size_t *bytes);
 

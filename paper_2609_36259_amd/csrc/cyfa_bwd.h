@@ -5,7 +5,7 @@
 
 namespace cyfa {
 
-constexpr int kBwdChunk = 16;       // tokens per chunk of the vector-ALU backward kernels
+constexpr int kBwdChunk = 16;       // chunk length a caller may name for the fp32 backward
 constexpr int kBwdMfmaChunk = 32;   // tokens per chunk of the matrix-core backward kernels
 constexpr int kBwdFinParts = 8;     // partial sums of the final-state loss per (b, h)
 

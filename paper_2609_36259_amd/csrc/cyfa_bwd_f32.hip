@@ -898,7 +898,7 @@ hipError_t launch_dtype(const BwdParams &p, const F32Ws &w, hipStream_t s) {
 
 // Layout (each piece 256-byte aligned): Mi + MiT, clk, cs, G, gam + wr + bet, gend, Kst,
 // Vst, DKe, DVe, U, dP, udu, dlam, dG, dMp, fin.
-size_t bwd_f32_workspace_bytes(int B, int T, int H, int dk, int dv) {
+static size_t need_bytes(int B, int T, int H, int dk, int dv) {
     const size_t BH = (size_t)B * H, nc = ((size_t)T + kTC - 1) / kTC, Tpad = nc * kTC;
     int per = 1;
     size_t n = align_up(2 * readout_f32_bytes(H));
@@ -913,6 +913,15 @@ size_t bwd_f32_workspace_bytes(int B, int T, int H, int dk, int dv) {
     if (nc > 0) n += align_up((size_t)readout_wgs(B, H, (int)nc, &per) * H * kR * kR * 4);
     n += align_up(BH * kBwdFinParts * 8);
     return n;
+}
+
+// Never less than the size the public header states (two states per 16 tokens and two
+// rows per token and head), which callers provision for by that formula.
+size_t bwd_f32_workspace_bytes(int B, int T, int H, int dk, int dv) {
+    const size_t BH = (size_t)B * H, nc = ((size_t)T + kBwdChunk - 1) / kBwdChunk;
+    const size_t stated = 2 * align_up(BH * nc * kR * (size_t)(dk + dv) * 4) + 2 * align_up(BH * nc * kBwdChunk * kR * 4);
+    const size_t need = need_bytes(B, T, H, dk, dv);
+    return need > stated ? need : stated;
 }
 
 hipError_t launch_bwd_f32(BwdParams p, void *ws, hipStream_t s) {

@@ -74,8 +74,9 @@ typedef enum {
     CYFA_KERNEL_AUTO = 0,  /* BF16 with d_k = d_v = 128 (m up to 255) or d_k =
                               d_v = 256 (m <= 127): matrix-core kernel; anything
                               else: the vector-ALU kernel                     */
-    CYFA_KERNEL_VALU = 1,  /* vector-ALU chunk kernel, fp32 arithmetic, any
-                              supported shape and dtype                        */
+    CYFA_KERNEL_VALU = 1,  /* fp32 arithmetic, any supported shape and dtype: the
+                              fp32 matrix instructions for m <= 127, the vector
+                              ALU for m > 127 or with segments = 1             */
     CYFA_KERNEL_MFMA = 2   /* matrix-core (bf16 MFMA) chunk kernel: BF16,
                               d_k = d_v = 128 (m up to 255) or d_k = d_v = 256
                               (m <= 127), chunk 32 or 64                       */

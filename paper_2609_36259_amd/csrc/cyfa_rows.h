@@ -53,12 +53,13 @@ size_t mfma_narrow_workspace_bytes(const FwdParams &p, int groups);
 hipError_t launch_fwd_mfma_narrow(const FwdParams &p, int groups, void *ws, hipStream_t st, hipEvent_t ev_start,
                                   hipEvent_t ev_stop);
 
-// Vector-ALU forward over chunk groups (d_k, d_v <= 128 and m <= 127; other
-// shapes run one group per sequence): groups > 1 forms the state entering each
-// group in ws (valu_group_workspace_bytes) before the chunk kernel.
+// Whether a vector-ALU or fp32 forward takes a segment count above one (d_k, d_v <= 128
+// and m <= 127).
 bool valu_groups_supported(const FwdParams &p);
-int valu_auto_groups(const FwdParams &p);
-size_t valu_group_workspace_bytes(const FwdParams &p, int groups);
-hipError_t launch_fwd_valu(const FwdParams &p, const float *M, int groups, void *ws, hipStream_t s);
+hipError_t launch_fwd_valu(const FwdParams &p, const float *M, hipStream_t s);
+
+// fp32 forward on the fp32 matrix instructions (m <= 127); forms its own readout matrix.
+size_t fwd_f32_workspace_bytes(const FwdParams &p);
+hipError_t launch_fwd_f32(const FwdParams &p, void *ws, hipStream_t s);
 
 }  // namespace cyfa

@@ -361,3 +361,45 @@ def test_valu_full_size_f32_chunk_groups():
     print("errors", {k: f"{v:.2e}" for k, v in errs.items()}, flush=True)
     for k, v in errs.items():
         assert v <= (1e-9 if k == "clock" else TOL_F32), (k, v)
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv,dtype", [
+    (1, 1, 1, 64, 64, "f32"), (2, 33, 1, 64, 128, "f32"), (1, 64, 2, 128, 64, "f32"),
+    (1, 65, 1, 256, 128, "f32"), (1, 97, 2, 64, 256, "bf16"),
+    (8, 130, 4, 256, 256, "f32"),                 # 256 workgroups: states walked, not scanned
+    (1, 4130, 1, 64, 64, "f32"),                  # more than 64 chunks: tables in their own launch
+])
+def test_f32_tile_forward_edges(B, T, H, dk, dv, dtype):
+    """The fp32 matrix-instruction forward at tile and chunk edges, from an initial state;
+    sampled sequences, all tokens, states, clocks and logits (fp32 sums: ~1e-6)."""
+    cyfa = _cyfa()
+    x = make_forward_inputs(B, T, H, dk, dv, seed=300 + T, dtype=dtype)
+    t = upload(x)
+    res = cyfa.forward(t["q"], t["k"], t["v"], t["delta"], t["log_alpha"], t["beta"], t["R"], scale=x["scale"],
+                       kernel=cyfa.KERNEL_VALU, return_state=True, return_logits=True)
+    pairs = list(range(B * H)) if B * H <= 4 else [0, 13, B * H - 1]
+    ref = run_oracle(x, pairs=pairs)
+    K, V = oracle_states_abs(ref, x["m"])
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    errs = dict(o=rel_err(pairs_view(res["o"], pairs, H), ref["o"]), z=rel_err(pairs_view(res["logits"], pairs, H), ref["z"]),
+                K=rel_err(state_view(res["K"], pairs, H), K), V=rel_err(state_view(res["V"], pairs, H), V))
+    print(errs)
+    assert max(errs.values()) <= tol, errs
+    assert clock_err(res["clock"].cpu().numpy().reshape(-1)[pairs], ref["lam"], x["m"]) <= 1e-9
+
+
+def test_f32_forward_nan_stays_causal():
+    """A NaN in v, k and q of one token reaches no earlier token's output."""
+    cyfa = _cyfa()
+    x = make_forward_inputs(1, 96, 1, 64, 64, seed=311, dtype="f32")
+    t = upload(x)
+    run = lambda **kw: cyfa.forward(*(kw.get(n, t[n]) for n in ("q", "k", "v", "delta", "log_alpha", "beta", "R")),  # noqa: E731
+                                    scale=x["scale"])
+    clean = run()
+    for name in ("q", "k", "v"):
+        for at in (5, 40, 77):
+            bad = t[name].clone()
+            bad[0, at, 0, 3] = float("nan")
+            o = run(**{name: bad})
+            assert (o[:, :at] - clean[:, :at]).abs().max() < 1e-5, (name, at)
+            assert torch.isnan(o[0, at, 0]).any(), (name, at)

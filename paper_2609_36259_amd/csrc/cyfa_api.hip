@@ -635,8 +635,9 @@ cyfa_status run_decode(const cyfa_dec_desc *desc, const void *q, const void *k, 
     p.scale = desc->scale; p.dtype = desc->dtype;
     p.q = q; p.k = k; p.v = v; p.delta = delta; p.log_alpha = log_alpha; p.beta = beta; p.R = R;
     p.K = K; p.V = V; p.clock = clock; p.o = o; p.logits = logits_out;
-    hipError_t e = p.m > cyfa::kMaxActive ? cyfa::launch_readout_prep_wide(p.H, p.m, R, M, s)
-                                          : cyfa::launch_readout_prep(p.H, p.m, R, M, nullptr, 1.f, s);
+    hipError_t e = hipSuccess;
+    if (p.m > cyfa::kMaxActive) e = cyfa::launch_readout_prep_wide(p.H, p.m, R, M, s);
+    else if (!cyfa::decode_fused(p)) e = cyfa::launch_readout_prep(p.H, p.m, R, M, nullptr, 1.f, s);
     if (e == hipSuccess) e = mark(g_ev_start, s);
     if (e == hipSuccess) e = cyfa::launch_decode(p, M, s);
     if (e == hipSuccess) e = mark(g_ev_stop, s);

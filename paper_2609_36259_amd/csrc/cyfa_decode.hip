@@ -19,6 +19,12 @@
 
 namespace cyfa {
 
+// Up to one workgroup per compute unit the step is a chain of latencies, and the launch
+// that forms M = R Phi is most of it: 16 streams x 16 heads take 20.1 us with the
+// transforms in the step, 22 us with that launch before it (1 stream: 14.1 against 16.2).
+// Beyond, workgroups queue and each one's longer life counts: 32 x 16 37 us against 32.
+bool decode_fused(const DecParams &p) { return p.m <= kMaxActive && (long long)p.N * p.H <= 256; }
+
 namespace {
 
 typedef float f32x4_nt __attribute__((ext_vector_type(4)));
@@ -31,7 +37,10 @@ __device__ __forceinline__ void store_stream(float4 *p, float4 v) {
 // 8 readout-matrix rows per thread at d = 128), sixteen for 256 rows.
 __host__ __device__ constexpr int dec_threads(int rows) { return rows > kStoreRows ? 1024 : 512; }
 
-template <int DK, int DV, int ROWS, typename Tin>
+// FUSED (128 rows): the kernel reads R itself and applies the Fourier basis to the two
+// vectors, z = R (Phi x) and y = Phi^T (R^T w), instead of reading the readout matrix
+// M = R Phi that a launch of its own formed before; see launch_decode.
+template <int DK, int DV, int ROWS, bool FUSED, typename Tin>
 __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, const float *__restrict__ Mg) {
     constexpr int kThreads = dec_threads(ROWS);
     constexpr int KQ = DK / 4;                       // float4 per key-state row
@@ -50,6 +59,9 @@ __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, 
     __shared__ float4 ypart[kThreads / MQ][MQ];
     __shared__ float2 cs[ROWS / 2];
     __shared__ float4 opart[kThreads / 64][VQ];
+    // FUSED: cos and sin of 2 pi n / m, and partial sums of the transforms per wave
+    __shared__ float tabc[FUSED ? ROWS : 1], tabs[FUSED ? ROWS : 1];
+    __shared__ float2 dft[FUSED ? kThreads / 64 : 1][64];
 
     const int nh = blockIdx.x;
     const int h = nh % p.H;
@@ -87,6 +99,33 @@ __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, 
         ks[c] = load_as_float(k, (size_t)nh * DK + c);
     }
     for (int c = tid; c < DV; c += kThreads) vs[c] = load_as_float(v, (size_t)nh * DV + c);
+    // Thread (column quad cm = tid % 32, row group g = tid / 32) holds rows
+    // MIT g .. MIT g + MIT-1, columns 4 cm .. 4 cm + 3 of M (16-byte loads, a
+    // wave reading two whole rows per load) or of R; the same registers serve
+    // z = M x and y = M^T w.
+    const int cm = tid % MQ, g = tid / MQ;
+    float4 mreg[MIT];
+    if constexpr (FUSED) {
+        const float *Rh = p.R ? p.R + (size_t)h * m * m : nullptr;
+#pragma unroll
+        for (int r = 0; r < MIT; ++r) {
+            const int row = MIT * g + r;
+            float e[4];
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) {
+                const int col = 4 * cm + cc;
+                e[cc] = row < m && col < m ? (Rh ? Rh[row * m + col] : (row == col ? 1.f : 0.f)) : 0.f;
+            }
+            mreg[r] = make_float4(e[0], e[1], e[2], e[3]);
+        }
+        if (tid >= kThreads - ROWS && tid - (kThreads - ROWS) < m) {
+            const int n = tid - (kThreads - ROWS);
+            double sn, c;
+            sincospi(2.0 * (double)n / (double)m, &sn, &c);
+            tabc[n] = (float)c;
+            tabs[n] = (float)sn;
+        }
+    }
     if (tid < J) {
         float c, s;
         clock_phase(lam, tid + 1, m, &c, &s);
@@ -163,16 +202,42 @@ __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, 
         }
         xs[i] = x;
     }
-    // Thread (column quad cm = tid % 32, row group g = tid / 32) holds rows
-    // MIT g .. MIT g + MIT-1, columns 4 cm .. 4 cm + 3 of M (16-byte loads, a
-    // wave reading two whole rows per load); the same registers serve z = M x
-    // and y = M^T w.
-    const int cm = tid % MQ, g = tid / MQ;
-    const float4 *M4 = reinterpret_cast<const float4 *>(Mg + (size_t)h * ROWS * ROWS);
-    float4 mreg[MIT];
+    if constexpr (!FUSED) {
+        const float4 *M4 = reinterpret_cast<const float4 *>(Mg + (size_t)h * ROWS * ROWS);
 #pragma unroll
-    for (int r = 0; r < MIT; ++r) mreg[r] = M4[(size_t)(MIT * g + r) * MQ + cm];
+        for (int r = 0; r < MIT; ++r) mreg[r] = M4[(size_t)(MIT * g + r) * MQ + cm];
+    }
     __syncthreads();
+    if constexpr (FUSED) {
+        // Phi x at the slots s = lane and m - s, which share every cosine and differ in the
+        // sines' sign; wave w sums the frequencies 8 w + 1 .. 8 w + 8
+        float C = 0.f, S = 0.f;
+        int n = (8 * wave * lane) % m;
+#pragma unroll
+        for (int l = 8 * wave + 1; l <= 8 * wave + 8; ++l) {
+            n += lane;
+            if (n >= m) n -= m;
+            if (l <= J && lane <= J) {
+                C = fmaf(xs[2 * l - 1], tabc[n], C);
+                S = fmaf(xs[2 * l], tabs[n], S);
+            }
+        }
+        dft[wave][lane] = make_float2(C, S);
+        const float x0 = xs[0];
+        __syncthreads();
+        if (tid <= J) {
+            float2 t = dft[0][tid];
+#pragma unroll
+            for (int w = 1; w < kThreads / 64; ++w) {
+                t.x += dft[w][tid].x;
+                t.y += dft[w][tid].y;
+            }
+            const float dc = x0 / sqrtf((float)m), ac = sqrtf(2.f / (float)m);
+            xs[tid] = fmaf(ac, t.x + t.y, dc);
+            if (tid) xs[m - tid] = fmaf(ac, t.x - t.y, dc);
+        }
+        __syncthreads();                       // (entries m .. of xs are still 0)
+    }
     {
         const float4 x4 = make_float4(xs[4 * cm], xs[4 * cm + 1], xs[4 * cm + 2], xs[4 * cm + 3]);
 #pragma unroll
@@ -227,7 +292,54 @@ __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, 
         ypart[g][cm] = y4;
     }
     __syncthreads();
-    if (tid < ROWS) {
+    if constexpr (FUSED) {
+        // Phi^T (R^T w): the slots' sums first, then the transform back, wave w summing the
+        // slots 8 w + 1 .. 8 w + 8 with their mirrors; frequency l = lane + 1
+        if (tid < ROWS) {
+            const float *yp = reinterpret_cast<const float *>(&ypart[0][0]) + tid;
+            float t = 0.f;
+#pragma unroll
+            for (int gg = 0; gg < kThreads / MQ; ++gg) t += yp[gg * MQ * 4];
+            xs[tid] = t;
+        }
+        __syncthreads();
+        float C = 0.f, S = 0.f;
+        const int l = lane + 1;
+        int n = (8 * wave * l) % m;
+#pragma unroll
+        for (int sl = 8 * wave + 1; sl <= 8 * wave + 8; ++sl) {
+            n += l;
+            if (n >= m) n -= m;
+            if (sl <= J && l <= J) {
+                C = fmaf(xs[sl] + xs[m - sl], tabc[n], C);
+                S = fmaf(xs[sl] - xs[m - sl], tabs[n], S);
+            }
+        }
+        // lane 63 has no frequency (J <= 63): it sums the slots for the DC column instead
+        if (lane == 63)
+            for (int sl = 8 * wave + 1; sl <= 8 * wave + 8; ++sl)
+                if (sl <= J) C += xs[sl] + xs[m - sl];
+        dft[wave][lane] = make_float2(C, S);
+        const float t0 = xs[0];
+        __syncthreads();
+        if (tid < 64) {
+            float2 t = make_float2(t0, 0.f);
+#pragma unroll
+            for (int w = 0; w < kThreads / 64; ++w) {
+                t.x += dft[w][tid].x;
+                t.y += dft[w][tid].y;
+            }
+            const float ac = sqrtf(2.f / (float)m);
+            if (tid == 63) {
+                xs[0] = t.x / sqrtf((float)m);
+            } else if (l <= J) {               // o'' = U(-lambda) y
+                const float2 ph = cs[tid];
+                const float y0 = ac * t.x, y1 = ac * t.y;
+                xs[2 * l - 1] = ph.x * y0 + ph.y * y1;
+                xs[2 * l] = -ph.y * y0 + ph.x * y1;
+            }
+        }
+    } else if (tid < ROWS) {
         float y[2] = {0.f, 0.f};
         const int i = tid;
         // the rotation pairs paper columns (2jj+1, 2jj+2); column 0 is DC
@@ -285,13 +397,13 @@ __global__ __launch_bounds__(dec_threads(ROWS)) void decode_kernel(DecParams p, 
     if (tid == 0) p.clock[nh] = lam;
 }
 
-template <int DK, int DV, int ROWS>
+template <int DK, int DV, int ROWS, bool FUSED>
 hipError_t launch_rows(const DecParams &p, const float *M, hipStream_t s) {
     const dim3 grid(p.N * p.H), block(dec_threads(ROWS));
     if (p.dtype == 0)
-        hipLaunchKernelGGL((decode_kernel<DK, DV, ROWS, float>), grid, block, 0, s, p, M);
+        hipLaunchKernelGGL((decode_kernel<DK, DV, ROWS, FUSED, float>), grid, block, 0, s, p, M);
     else
-        hipLaunchKernelGGL((decode_kernel<DK, DV, ROWS, __hip_bfloat16>), grid, block, 0, s, p, M);
+        hipLaunchKernelGGL((decode_kernel<DK, DV, ROWS, FUSED, __hip_bfloat16>), grid, block, 0, s, p, M);
     return hipGetLastError();
 }
 
@@ -299,9 +411,10 @@ hipError_t launch_rows(const DecParams &p, const float *M, hipStream_t s) {
 template <int DK, int DV>
 hipError_t launch_typed(const DecParams &p, const float *M, hipStream_t s) {
     if constexpr (DK <= 128 && DV <= 128) {
-        if (p.m > kMaxActive) return launch_rows<DK, DV, kWideRows>(p, M, s);
+        if (p.m > kMaxActive) return launch_rows<DK, DV, kWideRows, false>(p, M, s);
     }
-    return launch_rows<DK, DV, kStoreRows>(p, M, s);
+    return decode_fused(p) ? launch_rows<DK, DV, kStoreRows, true>(p, M, s)
+                           : launch_rows<DK, DV, kStoreRows, false>(p, M, s);
 }
 
 template <int DK>

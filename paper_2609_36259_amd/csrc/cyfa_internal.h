@@ -49,6 +49,8 @@ inline size_t readout_f32_bytes(int H) { return (size_t)H * kStoreRows * kStoreR
 // ---- launchers (return hipSuccess or the launch error) -------------------
 hipError_t launch_readout_prep(int H, int m, const float *R, float *M, __bf16 *Mz, float mz_scale,
                                hipStream_t s);
+// decode_fused: the step forms what it needs of R itself, and launch_decode takes no M.
+bool decode_fused(const DecParams &p);
 hipError_t launch_decode(const DecParams &p, const float *M, hipStream_t s);
 
 // ---- device helpers --------------------------------------------------------

@@ -403,3 +403,32 @@ def test_f32_forward_nan_stays_causal():
             o = run(**{name: bad})
             assert (o[:, :at] - clean[:, :at]).abs().max() < 1e-5, (name, at)
             assert torch.isnan(o[0, at, 0]).any(), (name, at)
+
+
+@pytest.mark.parametrize("m", [3, 65, 127])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_decode_both_readout_routes(m, dtype):
+    """256 stream-heads (the transforms in the step) against 260 (the readout matrix formed
+    before it) on the same 64 streams, with and without R.  Two fp32 evaluations of the
+    same sums: 1e-5; a bf16 output may round the other way: 2^-8 of its largest entry."""
+    cyfa = _cyfa()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=g)  # noqa: E731
+    H, d = 4, 64
+    q, k, v = (rnd(65, H, d).to(dtype) for _ in range(3))
+    delta, la, beta = rnd(65, H).exp(), -rnd(65, H).abs(), torch.sigmoid(rnd(65, H))
+    K, V = rnd(65, H, 128, d), rnd(65, H, 128, d)
+    K[:, :, m:] = 0
+    V[:, :, m:] = 0
+    clock = m * torch.rand((65, H), device="cuda", dtype=torch.float64, generator=g)
+    for R in (torch.eye(m, device="cuda") + 0.1 * rnd(H, m, m), None):
+        outs = []
+        for n in (64, 65):
+            s = [x[:n].clone() for x in (q, k, v, delta, K, V, clock, la, beta)]
+            o, z = cyfa.decode_step(*s, R, m=m, return_logits=True)
+            outs.append((o[:64].float(), z[:64], s[4][:64], s[5][:64], s[6][:64]))
+        (oa, za, *sa), (ob, zb, *sb) = outs
+        assert all(torch.equal(x, y) for x, y in zip(sa, sb))
+        assert (za - zb).abs().max() <= 1e-5 * zb.abs().max()
+        assert (oa - ob).abs().max() <= (1e-5 if dtype == torch.float32 else 2.0 ** -8) * ob.abs().max()

@@ -251,11 +251,11 @@ cyfa_status check_mixer(const cyfa_mixer_desc *d) {
     return CYFA_OK;
 }
 
-// workspace of the layer forward beyond the forward's: the prologue's q, k, v when the
-// ShortConv runs in its own kernel
+// workspace of the layer forward beyond the forward's: the prologue's q, k, v and gates when
+// the ShortConv runs in its own kernel
 size_t mixer_qkv_bytes(const cyfa_fwd_desc *d, const cyfa_mixer_weights *mw) {
     if (mw->fuse_conv) return 0;
-    return 3 * round_up((size_t)d->B * d->T * d->H * 128 * 2);
+    return 3 * round_up((size_t)d->B * d->T * d->H * 128 * 2) + 3 * round_up((size_t)d->B * d->T * d->H * 4);
 }
 
 cyfa::MixParams mixer_params(const cyfa_mixer_desc *d) {
@@ -434,11 +434,14 @@ cyfa_status cyfa_forward_mixer(const cyfa_fwd_desc *desc, const cyfa_mixer_weigh
     mix.A = mw->A; mix.z_beta = mw->z_beta; mix.gate = mw->gate; mix.g_o = mw->norm_o;
     mix.K = mw->conv_size; mix.act = mw->conv_act; mix.eps = mw->eps; mix.fuse_conv = mw->fuse_conv;
     const void *q = q_in, *k = k_in, *v = v_in;
+    float *delta = nullptr, *log_alpha = nullptr, *beta = nullptr;
     if (!mw->fuse_conv && desc->T > 0) {
-        // ShortConv and QK RMSNorm in the streaming kernel, into the workspace past the
-        // forward's own part
+        // ShortConv, QK RMSNorm and the gates in the streaming kernel, into the workspace past
+        // the forward's own part.  The gates are 12 bytes per token and head there; formed in
+        // the pre-pass's and the forward's staging instead they lengthened every chunk.
         char *buf = static_cast<char *>(workspace) + plan.ws_bytes;
-        const size_t one = mixer_qkv_bytes(desc, mw) / 3;
+        const size_t one = round_up((size_t)desc->B * desc->T * desc->H * 128 * 2);
+        const size_t gate = round_up((size_t)desc->B * desc->T * desc->H * 4);
         cyfa::MixParams mp{};
         mp.B = desc->B; mp.T = desc->T; mp.H = desc->H; mp.dk = 128; mp.dv = 128;
         mp.K = mw->conv_size; mp.act = mw->conv_act; mp.eps = mw->eps; mp.dtype = CYFA_BF16;
@@ -446,11 +449,21 @@ cyfa_status cyfa_forward_mixer(const cyfa_fwd_desc *desc, const cyfa_mixer_weigh
         mp.wq = mw->conv_q; mp.wk = mw->conv_k; mp.wv = mw->conv_v; mp.gq = mw->norm_q; mp.gk = mw->norm_k;
         mp.lens = lens;
         mp.q_out = buf; mp.k_out = buf + one; mp.v_out = buf + 2 * one;
+        delta = reinterpret_cast<float *>(buf + 3 * one);
+        mp.z_delta = mw->z_delta; mp.b_delta = mw->b_delta; mp.delta = delta;
+        if (mw->z_alpha) {
+            log_alpha = reinterpret_cast<float *>(buf + 3 * one + gate);
+            mp.z_alpha = mw->z_alpha; mp.b_alpha = mw->b_alpha; mp.A = mw->A; mp.log_alpha = log_alpha;
+        }
+        if (mw->z_beta) {
+            beta = reinterpret_cast<float *>(buf + 3 * one + 2 * gate);
+            mp.z_beta = mw->z_beta; mp.beta = beta;
+        }
         hipError_t e = cyfa::launch_mixer_prologue(mp, static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(CYFA_ERR_LAUNCH, "mixer prologue launch: %s", hipGetErrorString(e));
         q = mp.q_out; k = mp.k_out; v = mp.v_out;
     }
-    return forward_impl(&d2, q, k, v, nullptr, nullptr, nullptr, R, lens, nullptr, K0, V0, clock0, out,
+    return forward_impl(&d2, q, k, v, delta, log_alpha, beta, R, lens, nullptr, K0, V0, clock0, out,
                         K_out, V_out, clock_out, logits_out, workspace, plan.ws_bytes, stream, &mix);
 }
 

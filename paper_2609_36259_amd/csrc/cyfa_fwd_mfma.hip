@@ -383,10 +383,10 @@ __device__ __forceinline__ void mix_load_gate(const MfmaArgs &a, int b, int h, i
 // transpose read, double-buffered so that a chunk needs one barrier.  Each wave
 // runs the chunk's clock and decay scans itself (lane = token) and passes the
 // per-token phase and amplitude through a private LDS row.
-// kMix (layer forward): 0 the plain operator; otherwise the gates come from their
-// projections, and with kMix = 1 the staged k and v rows are the raw projections,
-// which the mixer's ShortConv and k's RMSNorm turn into the operator's k and v in
-// LDS first (kMix = 2: k and v are the standalone prologue's).
+// kMix (layer forward): 0 the plain operator, also after the standalone prologue; 1 the
+// gates come from their projections and the staged k and v rows are the raw projections,
+// which the mixer's ShortConv and k's RMSNorm turn into the operator's k and v in LDS
+// first.
 template <int CC, int kMix = 0>
 __global__ __launch_bounds__(NT, 2) void segment_state_kernel(MfmaArgs a, float mz_scale) {
     constexpr int STILE = CC * SWS * 2;                // one swizzled K or V tile
@@ -812,7 +812,8 @@ __device__ __forceinline__ bf16x8 decay_rows(bf16x8 v, const float *dw) {
 // next chunk is prefetched into registers.
 // kMix: 0 the plain operator; 1 the layer forward with the mixer prologue in the
 // chunk staging and the epilogue on the output tile; 2 the layer forward after
-// the standalone prologue's ShortConv and RMSNorm (gates and epilogue fused here).
+// the standalone prologue (the epilogue fused here).  The gates used to be formed here and
+// in the pre-pass with 2 as well; from the prologue's launch they cost 3 MB of traffic.
 // See the mixer pieces above.
 template <int CC, int kMix>
 __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
@@ -878,7 +879,7 @@ __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
     // (needed by the first stage), then the entering states, which the first
     // chunk's products need only after its staging, scans and temporal writes.
     Prefetch<CC> pf;
-    load_chunk<CC, true, NT, kMix != 0>(p, b, h, c_begin * CC, Tb, tid, pf, &a.mix);
+    load_chunk<CC, true, NT, kMix == 1>(p, b, h, c_begin * CC, Tb, tid, pf, &a.mix);
     if constexpr (kMix != 0) mix_setup<kConv>(a, ML, smem, b, h, c_begin * CC, tid, NT);
     uint4 gpf[2];                                    // kMix: the chunk's gate rows
     {
@@ -948,7 +949,7 @@ __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
             *reinterpret_cast<uint4 *>(smem + Ly::V + offs) = fv[0];
             *reinterpret_cast<uint4 *>(smem + Ly::V + offs1) = fv[1];
         }
-        if (c + 1 < c_end) load_chunk<CC, true, NT, kMix != 0>(p, b, h, t0 + CC, Tb, tid, pf, &a.mix);
+        if (c + 1 < c_end) load_chunk<CC, true, NT, kMix == 1>(p, b, h, t0 + CC, Tb, tid, pf, &a.mix);
         // factor applied to the carried states this chunk, and whether the chunk's
         // decay is factored (the A tile then holds A_dec); uniform: scalar registers
         const float sf = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.ctl[0])));
@@ -1354,11 +1355,9 @@ hipError_t launch_cc(const MfmaArgs &a, int BHv, hipStream_t st, hipEvent_t ev_s
             a64.cps = a.cps / 2;
             a64.nchunks = (a.p.T + 63) / 64;
             if (mode == 1) pre(segment_state_kernel<64, 1>, a64);
-            else if (mode == 2) pre(segment_state_kernel<64, 2>, a64);
             else pre(segment_state_kernel<64, 0>, a64);
         } else {
             if (mode == 1) pre(segment_state_kernel<CC, 1>, a);
-            else if (mode == 2) pre(segment_state_kernel<CC, 2>, a);
             else pre(segment_state_kernel<CC, 0>, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;

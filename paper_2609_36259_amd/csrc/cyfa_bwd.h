@@ -7,7 +7,7 @@ namespace cyfa {
 
 constexpr int kBwdChunk = 16;       // chunk length a caller may name for the fp32 backward
 constexpr int kBwdMfmaChunk = 32;   // tokens per chunk of the matrix-core backward kernels
-constexpr int kBwdFinParts = 8;     // partial sums of the final-state loss per (b, h)
+constexpr int kBwdFinParts = 16;    // partial sums of the final-state loss per (b, h)
 
 // Gradients of L = sum_t <do_t, o_t> + <dK_T, Kbar_T> + <dV_T, Vbar_T>.
 struct BwdParams {
@@ -31,7 +31,7 @@ struct BwdParams {
     float *U, *dP;                  // [BH][Tpad] readout output u_t and key-pass adjoint dp_t (fp32 backward)
     float *udu, *dlam, *dG;         // [BH][Tpad] <u_t, du_t>, dL/dlambda_t, dL/dG_t
     float *dMp;                     // [BH][groups][128][128] partial dL/dM
-    double *fin;                    // [BH][8] partial sums of <dK_T, Kbar_T> + <dV_T, Vbar_T>
+    double *fin;                    // [BH][kBwdFinParts] partial sums of <dK_T, Kbar_T> + <dV_T, Vbar_T>
 };
 
 // The last two kernels of either backward: reverse cumulative sums of p.dG and

@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(kNT, 1) void readout_kernel(Args a) {
         for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
         if (lane == 0) {
             p.fin[(size_t)bh * kCombBlocks + w] = t;
-            p.fin[(size_t)bh * kCombBlocks + 4 + w] = 0.0;
+            for (int u = 4 + w; u < kCombBlocks; u += 4) p.fin[(size_t)bh * kCombBlocks + u] = 0.0;
         }
     }
     // the group's dM in paper column order

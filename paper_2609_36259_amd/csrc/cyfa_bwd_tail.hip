@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kNT) void bwd_scan_kernel(BwdParams p) {
 // (6) dR_h = (sum over sequences b and chunk groups of dM) Phi^T on the active
 // m x m block (M = R Phi, Phi the real Fourier basis of App. A.1).  Workgroup
 // (h, row block) handles kDRRows rows of dR, which need the same rows of dM only.
-constexpr int kDRRows = 8;
+constexpr int kDRRows = 4;          // one element per thread (8: 16 us against 9 at H = 4, its chain of loads twice as long)
 __global__ __launch_bounds__(kNT) void bwd_dR_kernel(BwdParams p, int nb) {
     __shared__ float dM[kDRRows][kLD];
     __shared__ float tab[2][kStoreRows];

@@ -340,17 +340,19 @@ __global__ __launch_bounds__(256, 4) void f32_states_kernel(BwdParams p, F32Ws w
 }
 
 // Combines the chunks' own contributions in place, element by element: slot c becomes
-// the state entering chunk c (the adjoint at its end, in reverse).  Eight chunks'
-// loads are in flight at a time; only the multiply-add is a chain.
+// the state entering chunk c (the adjoint at its end, in reverse).  Sixteen chunks'
+// loads are in flight at a time; only the multiply-add is a chain.  The first half of a
+// sequence's workgroups takes the key state, the second the value state.
 template <int DK, int DV, bool ADJ>
 __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
     __shared__ double red[4];
+    constexpr int kHalf = kBwdFinParts / 2;
     const int bh = blockIdx.x, tid = threadIdx.x, m = p.m, nc = p.nc;
     const float *ge = w.gend + (size_t)bh * nc;
     double fin = 0.0;
     auto run = [&](int D, float *slots, const float *ext, const float *fext, float *gext) {
         const size_t st = (size_t)kR * D / 4;
-        for (int e = blockIdx.y * 256 + tid; e < kR * D / 4; e += 256 * kBwdFinParts) {
+        for (int e = (blockIdx.y % kHalf) * 256 + tid; e < kR * D / 4; e += 256 * kHalf) {
             // four basis rows i0 .. + 3 of channel ch
             const int blk = e >> 8, l = e & 63, i0 = 32 * (blk / (D / 32)) + 8 * ((e >> 6) & 3) + 4 * (l >> 5);
             const int ch = 32 * (blk % (D / 32)) + (l & 31);
@@ -363,17 +365,17 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
             if (ext)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) E[q] = ext_at(q) >= 0 ? ext[ext_at(q)] : 0.f;
-            for (int c0 = 0; c0 < nc; c0 += 8) {
-                f32x4 own[8];
-                float g[8];
+            for (int c0 = 0; c0 < nc; c0 += 16) {
+                f32x4 own[16];
+                float g[16];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
+                for (int u = 0; u < 16; ++u) {
                     const int c = min(c0 + u, nc - 1), cc = ADJ ? nc - 1 - c : c;
                     own[u] = s[cc * st];
                     g[u] = ge[cc];
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
+                for (int u = 0; u < 16; ++u) {
                     if (c0 + u >= nc) break;
                     s[(ADJ ? nc - 1 - (c0 + u) : c0 + u) * st] = E;
 #pragma unroll
@@ -390,8 +392,10 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
             }
         }
     };
-    run(DK, ADJ ? w.DKe : w.Kst, ADJ ? p.dK_T : p.K0, p.dK_T, ADJ ? p.gK0 : w.Ko);
-    run(DV, ADJ ? w.DVe : w.Vst, ADJ ? p.dV_T : p.V0, p.dV_T, ADJ ? p.gV0 : w.Vo);
+    if (blockIdx.y < kHalf)
+        run(DK, ADJ ? w.DKe : w.Kst, ADJ ? p.dK_T : p.K0, p.dK_T, ADJ ? p.gK0 : w.Ko);
+    else
+        run(DV, ADJ ? w.DVe : w.Vst, ADJ ? p.dV_T : p.V0, p.dV_T, ADJ ? p.gV0 : w.Vo);
     if (ADJ || !p.fin) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) fin += __shfl_xor(fin, o);

@@ -387,17 +387,18 @@ __device__ __forceinline__ void mix_load_gate(const MfmaArgs &a, int b, int h, i
 // gates come from their projections and the staged k and v rows are the raw projections,
 // which the mixer's ShortConv and k's RMSNorm turn into the operator's k and v in LDS
 // first.
-template <int CC, int kMix = 0>
+// kDirect: MfmaArgs::direct (a template argument, so that the scan's route keeps its code).
+template <int CC, int kMix, bool kDirect>
 __global__ __launch_bounds__(NT, 2) void segment_state_kernel(MfmaArgs a, float mz_scale) {
     constexpr int STILE = CC * SWS * 2;                // one swizzled K or V tile
     constexpr int KIT = CC * 16 / NT;                  // 16-byte pieces per thread per tensor
     constexpr int RPP = NT / 16;                       // tile rows per pass
     constexpr int SCB = 4 * STILE;                     // per-wave (phase, amplitude) rows
-    constexpr int MIX0 = SCB + 4 * 64 * 8 + 4 * 8;     // kMix: taps, halo, RMSNorm weights
+    constexpr int MIX0 = SCB + 4 * 64 * 8 + 8 * 8;     // kMix: taps, halo, RMSNorm weights
     __shared__ __attribute__((aligned(256)))
     char smem[MIX0 + (kMix == 1 ? kMixTapBytes + kMixHaloBytes + kMixNormBytes : 0)];
     const MixLds ML{MIX0, MIX0 + kMixTapBytes, MIX0 + kMixTapBytes + kMixHaloBytes};
-    static_assert(SCB + 4 * 64 * 8 + 4 * 8 >= prep_lds_bytes(kPrepRows), "readout-matrix blocks fit");
+    static_assert(SCB + 4 * 64 * 8 + 8 * 8 >= prep_lds_bytes(kPrepRows), "readout-matrix blocks fit");
     const FwdParams &p = a.p;
     const int Pm1 = a.P - 1;
     const int Hv = p.H * a.hv;                         // (virtual) heads of 128 channels
@@ -483,6 +484,19 @@ __global__ __launch_bounds__(NT, 2) void segment_state_kernel(MfmaArgs a, float 
     }
     gpart = lane63(wave_incl_scan(gpart));
     if (lane == 0) red[w] = gpart;
+    // the absolute clock at the segment's start, where no scan forms it
+    if constexpr (kDirect) {
+        double dpart = 0.0;
+        for (int t = tid; t < min(t_begin, Tb); t += NT) {
+            const size_t si = (seq_row0(p, b) + t) * p.H + h;
+            if constexpr (kMix)
+                dpart += (double)mix_sigm(a.mix.z_delta[si] + (a.mix.b_delta ? a.mix.b_delta[h] : 0.f));
+            else
+                dpart += (double)p.delta[si];
+        }
+        dpart = lane63(wave_incl_scan(dpart));
+        if (lane == 0) red[4 + w] = dpart;
+    }
 
     lds_barrier();                                     // (the chunk's loads stay in flight)
     const double G_end = (red[0] + red[1]) + (red[2] + red[3]);
@@ -494,6 +508,8 @@ __global__ __launch_bounds__(NT, 2) void segment_state_kernel(MfmaArgs a, float 
         vacc[x] = zero_acc();
     }
     double carry = 0.0, gsum = 0.0;
+    if constexpr (kDirect)
+        carry = reduce_clock((p.clock0 ? p.clock0[bh / a.hv] : 0.0) + ((red[4] + red[5]) + (red[6] + red[7])), m);
     const int trs = tr_off_swz(lane);
     for (int c = c_begin; c < c_end; ++c) {
         const int buf = (c - c_begin) & 1;
@@ -584,6 +600,7 @@ __global__ __launch_bounds__(NT, 2) void segment_state_kernel(MfmaArgs a, float 
     if (tid == 0) {
         a.seg_span[slot] = carry;
         a.seg_gsum[slot] = G_end;
+        if constexpr (kDirect) a.seg_origin[slot + 1] = carry;
     }
 }
 
@@ -815,7 +832,7 @@ __device__ __forceinline__ bf16x8 decay_rows(bf16x8 v, const float *dw) {
 // the standalone prologue (the epilogue fused here).  The gates used to be formed here and
 // in the pre-pass with 2 as well; from the prologue's launch they cost 3 MB of traffic.
 // See the mixer pieces above.
-template <int CC, int kMix>
+template <int CC, int kMix, bool kDirect>
 __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
     static_assert(CC == 32, "four-wave fused kernel: 32-token chunks");
     using Ly = Lay<CC>;
@@ -895,7 +912,9 @@ __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
     }
     f32x16 kacc[4], vacc[4];
     const __bf16 *slot_state = a.seg_state + ((size_t)bh * a.P + seg) * kStateFloats;
-    if (a.has_init && !(seg == 0 && a.zero_init)) {
+    if constexpr (kDirect) {
+        sum_entering(a, bh, seg, w, lane, kacc, vacc);
+    } else if (a.has_init && !(seg == 0 && a.zero_init)) {
         load_state(slot_state, w, lane, kacc, vacc);
     } else {
 #pragma unroll
@@ -904,7 +923,7 @@ __global__ __launch_bounds__(NT, 2) void chunk_forward_kernel(MfmaArgs a) {
             vacc[x] = f32x16{};
         }
     }
-    double carry = 0.0, gsum = 0.0;
+    double carry = kDirect ? entering_clock(a, bh, bh, seg) : 0.0, gsum = 0.0;
     float logf = 0.f;                                // carried states are exp(logf) x registers
     __bf16 *o = static_cast<__bf16 *>(p.o);
 
@@ -1241,7 +1260,7 @@ __global__ __launch_bounds__(NT) void state_out_kernel(MfmaArgs a) {
     const int j = (pr.i0 >> 1) + 1;
     const size_t slot = (size_t)bh * a.P + (a.P - 1);
     const float *st = a.fin_state + (size_t)bh * kStateFloats;
-    const double origin = a.seg_origin[slot];
+    const double origin = a.direct ? 0.0 : a.seg_origin[slot];
     // ABI state [B][H][128][128 hv]: column block bh mod hv of head bh / hv
     const int dabi = 128 * a.hv;
     const size_t base = (size_t)(bh / a.hv) * 128 * dabi + 128 * (bh % a.hv) + pr.col;
@@ -1354,15 +1373,17 @@ hipError_t launch_cc(const MfmaArgs &a, int BHv, hipStream_t st, hipEvent_t ev_s
             a64.chunk = 64;
             a64.cps = a.cps / 2;
             a64.nchunks = (a.p.T + 63) / 64;
-            if (mode == 1) pre(segment_state_kernel<64, 1>, a64);
-            else pre(segment_state_kernel<64, 0>, a64);
+            if (mode == 1) a.direct ? pre(segment_state_kernel<64, 1, true>, a64) : pre(segment_state_kernel<64, 1, false>, a64);
+            else a.direct ? pre(segment_state_kernel<64, 0, true>, a64) : pre(segment_state_kernel<64, 0, false>, a64);
         } else {
-            if (mode == 1) pre(segment_state_kernel<CC, 1>, a);
-            else pre(segment_state_kernel<CC, 0>, a);
+            if (mode == 1) a.direct ? pre(segment_state_kernel<CC, 1, true>, a) : pre(segment_state_kernel<CC, 1, false>, a);
+            else a.direct ? pre(segment_state_kernel<CC, 0, true>, a) : pre(segment_state_kernel<CC, 0, false>, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (a.has_init) {
+    if (a.direct) {
+        // the pre-pass left everything the fused kernel needs
+    } else if (a.has_init) {
         const int nscan = BHv * kScanBlocks;
         const int nprep = prepass ? 0 : a.p.H * (kStoreRows / kPrepRows);
         hipLaunchKernelGGL(scan_prep_kernel, dim3(nscan + nprep), dim3(NT), 0, st, a, nscan, mz_scale);
@@ -1380,9 +1401,9 @@ hipError_t launch_cc(const MfmaArgs &a, int BHv, hipStream_t st, hipEvent_t ev_s
         auto fused = [&](auto kern) {
             hipExtLaunchKernelGGL(kern, dim3(BHv * a.P), dim3(NT), 0, st, ev_start, ev_stop, 0, a);
         };
-        if (mode == 1) fused(chunk_forward_kernel<CC, 1>);
-        else if (mode == 2) fused(chunk_forward_kernel<CC, 2>);
-        else fused(chunk_forward_kernel<CC, 0>);
+        if (mode == 1) a.direct ? fused(chunk_forward_kernel<CC, 1, true>) : fused(chunk_forward_kernel<CC, 1, false>);
+        else if (mode == 2) a.direct ? fused(chunk_forward_kernel<CC, 2, true>) : fused(chunk_forward_kernel<CC, 2, false>);
+        else a.direct ? fused(chunk_forward_kernel<CC, 0, true>) : fused(chunk_forward_kernel<CC, 0, false>);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         if (ev_start && (e = hipEventRecord(ev_start, st)) != hipSuccess) return e;
@@ -1435,6 +1456,15 @@ hipError_t launch_fwd_mfma(const FwdParams &p, int P, void *ws, hipStream_t st,
     a.zero_init = (p.K0 || p.V0) ? 0 : 1;
     a.hv = virtual_heads(p);
     if (mix) a.mix = *mix;
+    // With two to four segments and no initial state, each segment's workgroup sums the
+    // earlier contributions in its prologue and the scan between the pre-pass and the
+    // fused kernel (14 .. 16 us) is saved: B 32, T 2048, H 4, d 256 (two segments) 273 ->
+    // 264 us, B 8, T 2048, H 16, d 128 (four) 161 -> 155 us.  A contribution costs the last
+    // segment's workgroup about 4 us: with eight segments the call took 176 us against 166.
+    // Initial states add one more to every workgroup (B 16, T <= 1024, packed, H 16, two
+    // segments: 212 against 203 us) and stay with the scan.  The pre-pass then sums the
+    // increments before its segment itself, which the bound on T keeps short.
+    a.direct = a.P > 1 && a.P <= 4 && a.zero_init && a.nchunks > 0 && p.T <= 8192;
     const int BHv = p.B * p.H * a.hv;
 
     hipError_t e = launch_cc<32>(a, BHv, st, ev_start, ev_stop);

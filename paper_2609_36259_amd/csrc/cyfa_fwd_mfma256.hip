@@ -184,6 +184,7 @@ __device__ __forceinline__ void scale4(f32x16 (&acc)[4], float f) {
         for (int v = 0; v < 16; ++v) acc[x][v] *= f;
 }
 
+template <bool kDirect>
 __global__ __launch_bounds__(kNT8, 1) void chunk_forward256_kernel(MfmaArgs a) {
     using L = Lay2;
     constexpr int SSC = L::SSC;
@@ -250,7 +251,9 @@ __global__ __launch_bounds__(kNT8, 1) void chunk_forward256_kernel(MfmaArgs a) {
     // that virtual head's pairs (index 2 bh + dh), in the same dump layout.
     f32x16 kacc[4], vacc[4];
     const size_t vh = (size_t)bh * 2 + dh;
-    if (a.has_init && !(seg == 0 && a.zero_init)) {
+    if constexpr (kDirect) {
+        sum_entering(a, vh, seg, sb, lane, kacc, vacc);
+    } else if (a.has_init && !(seg == 0 && a.zero_init)) {
         load_state(a.seg_state + (vh * a.P + seg) * kStateFloats, sb, lane, kacc, vacc);
     } else {
 #pragma unroll
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(kNT8, 1) void chunk_forward256_kernel(MfmaArgs a) {
             vacc[x] = f32x16{};
         }
     }
-    double carry = 0.0, gsum = 0.0;
+    double carry = kDirect ? entering_clock(a, bh, vh, seg) : 0.0, gsum = 0.0;
     float logf = 0.f;
     __bf16 *o = static_cast<__bf16 *>(p.o);
 
@@ -493,8 +496,10 @@ __global__ __launch_bounds__(kNT8, 1) void chunk_forward256_kernel(MfmaArgs a) {
 }  // namespace
 
 hipError_t launch_chunk256(const MfmaArgs &a, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    hipExtLaunchKernelGGL(chunk_forward256_kernel, dim3(a.p.B * a.p.H * a.P), dim3(kNT8), 0, st, ev_start,
-                          ev_stop, 0, a);
+    auto go = [&](auto kern) {
+        hipExtLaunchKernelGGL(kern, dim3(a.p.B * a.p.H * a.P), dim3(kNT8), 0, st, ev_start, ev_stop, 0, a);
+    };
+    a.direct ? go(chunk_forward256_kernel<true>) : go(chunk_forward256_kernel<false>);
     return hipGetLastError();
 }
 

@@ -21,7 +21,10 @@ struct MfmaArgs {
     double *seg_span;    // [B*H*P] clock span of each segment (reduced mod m)
     double *seg_gsum;    // [B*H*P] sum of log alpha over each segment
     double *seg_origin;  // [B*H*P] absolute clock at each segment start (reduced)
-    double *final_lam;   // [B*H] local clock after the last segment (reduced)
+    double *final_lam;   // [B*H] local clock after the last segment (reduced; absolute if direct)
+    int direct;          // no scan (zero_init only): contributions and chunk clocks are absolute,
+                         // seg_origin comes from the pre-pass (segments 1 ..), and each segment's
+                         // workgroup sums the earlier contributions itself
     int has_init;        // segment-entry states are read from seg_state
     int zero_init;       // no initial state: the first segment starts from zero (its entry
                          // state is neither written by the scan nor read)
@@ -88,6 +91,46 @@ __device__ __forceinline__ void load_state(const __bf16 *st, int w, int lane, f3
             vacc[x][v + 8] = (float)v1[v];
         }
     }
+}
+
+// The state entering segment seg without a scan (MfmaArgs::direct): the earlier segments'
+// contributions, each decayed through the segments after it.
+__device__ __forceinline__ void sum_entering(const MfmaArgs &a, size_t vh, int seg, int w, int lane,
+                                             f32x16 (&kacc)[4], f32x16 (&vacc)[4]) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        kacc[x] = f32x16{};
+        vacc[x] = f32x16{};
+    }
+    double sum = 0.0;                                // log decay from contribution q's end
+#pragma unroll 1
+    for (int q = seg - 1; q >= 0; --q) {
+        const __bf16 *st = a.seg_state + (vh * a.P + q) * kStateFloats;
+        const float f = __expf((float)sum);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            bf16x8 s[4][2];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    s[x][u] = *reinterpret_cast<const bf16x8 *>(st + 128 * 128 * half + dump_off(w, x, lane, 8 * u));
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    if (half) vacc[x][v] = fmaf(f, (float)s[x][v >> 3][v & 7], vacc[x][v]);
+                    else kacc[x][v] = fmaf(f, (float)s[x][v >> 3][v & 7], kacc[x][v]);
+                }
+        }
+        sum += a.seg_gsum[vh * a.P + q];
+    }
+}
+
+// clock entering segment seg of (b, h) = bh, with MfmaArgs::direct
+__device__ __forceinline__ double entering_clock(const MfmaArgs &a, int bh, size_t vh, int seg) {
+    if (seg > 0) return a.seg_origin[vh * a.P + seg];
+    return a.p.clock0 ? reduce_clock(a.p.clock0[bh], a.p.m) : 0.0;
 }
 
 // fp32 dump (the final state), four 16-byte stores per accumulator

@@ -251,3 +251,28 @@ def test_resume_in_place(kernel, segments):
     assert torch.equal(got["o"], ref["o"])
     assert torch.equal(K, ref["K"]) and torch.equal(V, ref["V"])
     assert torch.equal(clk, ref["clock"])
+
+
+@pytest.mark.parametrize("d,H", [(128, 2), (256, 1)])
+@pytest.mark.parametrize("segments", [2, 3, 4, 5])
+def test_entering_states_without_a_scan(d, H, segments):
+    """Two to four segments with no initial state sum the earlier contributions in the fused
+    kernel, five take the scan: against the fp32 forward from the same clock, with lengths
+    that end in every segment (0, 1, inside, at a segment's edge, full)."""
+    cyfa = _cyfa()
+    T = 32 * 11 + 7
+    per = 32 * -(-12 // segments)
+    x = make_forward_inputs(6, T, H, d, d, seed=120 + segments, dtype="bf16")
+    t = upload(x)
+    lens = torch.tensor([T, 0, 1, per, per + 3, min(T, 2 * per)], dtype=torch.int32, device="cuda")
+    clock0 = torch.linspace(-3.0, 500.0, 6 * H, dtype=torch.float64, device="cuda").reshape(6, H)
+    run = lambda **kw: cyfa.forward(t["q"], t["k"], t["v"], t["delta"], t["log_alpha"], t["beta"], t["R"],  # noqa: E731
+                                    scale=x["scale"], lens=lens, clock0=clock0, return_state=True, **kw)
+    a, b = run(kernel=cyfa.KERNEL_MFMA, segments=segments), run(kernel=cyfa.KERNEL_VALU)
+    live = lambda o: torch.cat([o[i, :n] for i, n in enumerate(lens.tolist())]).float().cpu()  # noqa: E731
+    assert rel_err(live(a["o"]), live(b["o"])) <= TOL_BF16
+    for key in ("K", "V"):
+        for i, n in enumerate(lens.tolist()):
+            assert rel_err(a[key][i].cpu(), b[key][i].cpu()) <= TOL_BF16, (key, i, n)
+    dc = torch.remainder(a["clock"] - b["clock"], x["m"])
+    assert torch.minimum(dc, x["m"] - dc).max() <= 1e-9

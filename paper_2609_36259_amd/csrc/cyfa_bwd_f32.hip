@@ -293,7 +293,7 @@ template <int DK, int DV, typename Tin>
 __global__ __launch_bounds__(128, 1) void f32_grad_kernel(BwdParams p, F32Ws w) {
     __shared__ __attribute__((aligned(16))) float Sqk[kTC][kLS], Sdov[kTC][kLS], Sdpa[kTC][kLS], Sua[kTC][kLS];
     __shared__ __attribute__((aligned(16))) float tiles[2 * kLdsTile];
-    const int c = blockIdx.x, bh = blockIdx.y, b = bh / p.H, hd = bh % p.H, tid = threadIdx.x, m = p.m;
+    const int c = blockIdx.x % p.nc, bh = blockIdx.x / p.nc, b = bh / p.H, hd = bh % p.H, tid = threadIdx.x, m = p.m;
     const int lane = tid & 63, l31 = lane & 31, h = lane >> 5, tb = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Tb = bwd_tokens(p, b), left = min(Tb - c * kTC, kTC);
     const size_t grow = first_row(p, b) + c * kTC, row0 = (size_t)bh * p.Tpad + c * kTC;
@@ -512,7 +512,7 @@ hipError_t launch_typed(const BwdParams &p, const F32Ws &w, hipStream_t s) {
         hipLaunchKernelGGL((f32_readout_kernel<DK, DV, Tin>), dim3(p.H, nu), dim3(256), 0, s, p, w, per);
     }
     launch_states<DK, DV, Tin, true>(p, w, s);
-    if (p.nc > 0) hipLaunchKernelGGL((f32_grad_kernel<DK, DV, Tin>), dim3(p.nc, BH), dim3(128), 0, s, p, w);
+    if (p.nc > 0) hipLaunchKernelGGL((f32_grad_kernel<DK, DV, Tin>), dim3(p.nc * BH), dim3(128), 0, s, p, w);
     BwdParams tail = p;
     tail.groups = 1;                // dMp is [nu][H][128][128]
     return launch_bwd_tail(tail, nu, s);

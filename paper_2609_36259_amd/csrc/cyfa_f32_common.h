@@ -119,7 +119,7 @@ __device__ __forceinline__ void chunk_tables(const BwdParams &p, const F32Ws &w,
 
 __global__ __launch_bounds__(256) void f32_tables_kernel(BwdParams p, F32Ws w) {
     __shared__ double rev[kTC];
-    chunk_tables(p, w, blockIdx.x, blockIdx.y, false, rev);
+    chunk_tables(p, w, blockIdx.x % p.nc, blockIdx.x / p.nc, false, rev);
 }
 
 __global__ __launch_bounds__(256) void f32_prep_kernel(BwdParams p, F32Ws w) {
@@ -416,11 +416,13 @@ void launch_states(const BwdParams &p, const F32Ws &w, hipStream_t s) {
     hipLaunchKernelGGL((f32_scan_kernel<DK, DV, ADJ>), dim3(BH, kBwdFinParts), dim3(256), 0, s, p, w);
 }
 
+// (chunk, sequence) grids here are flat: a grid's y and z hold 65535 blocks only, and a batch
+// may have more sequences.
 inline void launch_front(const BwdParams &p, const F32Ws &w, hipStream_t s) {
     const int BH = p.B * p.H, base = p.H * (kR / kPrepRows) + BH;
     const bool one = p.nc <= kTableChunks;
     hipLaunchKernelGGL(f32_prep_kernel, dim3(base + (one ? BH * p.nc : 0)), dim3(256), 0, s, p, w);
-    if (!one) hipLaunchKernelGGL(f32_tables_kernel, dim3(p.nc, BH), dim3(256), 0, s, p, w);
+    if (!one) hipLaunchKernelGGL(f32_tables_kernel, dim3(p.nc * BH), dim3(256), 0, s, p, w);
 }
 
 inline size_t align_up(size_t x) { return (x + 255) / 256 * 256; }

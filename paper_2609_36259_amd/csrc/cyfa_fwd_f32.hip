@@ -46,7 +46,8 @@ template <int DK, int DV, typename Tin>
 __global__ __launch_bounds__(256, 2) void f32_forward_kernel(BwdParams p, F32Ws w, void *out, float *logits) {
     __shared__ __attribute__((aligned(16))) float xs[4096], ws[4096], part[4096], tiles[4 * kLdsTile];
     __shared__ float red[2][4][32];
-    const int c = blockIdx.x >> 1, tb = blockIdx.x & 1, bh = blockIdx.y, b = bh / p.H, hd = bh % p.H;
+    const int per_seq = (p.T + 31) / 32, tile = blockIdx.x % per_seq, bh = blockIdx.x / per_seq;
+    const int c = tile >> 1, tb = tile & 1, b = bh / p.H, hd = bh % p.H;
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l31 = lane & 31, h = lane >> 5, lane4 = 4 * lane, m = p.m;
     const int left = min(bwd_tokens(p, b) - c * kTC, kTC);
@@ -187,7 +188,7 @@ hipError_t launch_typed(const BwdParams &p, const F32Ws &w, void *out, float *lo
     launch_front(p, w, s);
     launch_states<DK, DV, Tin, false>(p, w, s);
     if (p.nc > 0)
-        hipLaunchKernelGGL((f32_forward_kernel<DK, DV, Tin>), dim3((p.T + 31) / 32, p.B * p.H), dim3(256), 0, s, p, w, out,
+        hipLaunchKernelGGL((f32_forward_kernel<DK, DV, Tin>), dim3((p.T + 31) / 32 * (p.B * p.H)), dim3(256), 0, s, p, w, out,
                            logits);
     return hipGetLastError();
 }

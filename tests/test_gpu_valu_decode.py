@@ -388,6 +388,24 @@ def test_f32_tile_forward_edges(B, T, H, dk, dv, dtype):
     assert clock_err(res["clock"].cpu().numpy().reshape(-1)[pairs], ref["lam"], x["m"]) <= 1e-9
 
 
+def test_f32_more_sequences_than_a_grid_axis():
+    """65540 sequences (a grid's second axis holds 65535): forward and backward of the last
+    ones as in a batch of their own, bit for bit."""
+    cyfa = _cyfa()
+    B, T, H, d = 16385, 2, 4, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q, k, v, d_o = (torch.randn((B, T, H, d), device="cuda", generator=g) for _ in range(4))
+    la, delta = -torch.rand((B, T, H), device="cuda", generator=g), torch.rand((B, T, H), device="cuda", generator=g)
+    got = cyfa.forward(q, k, v, delta, la)
+    grads = cyfa.backward(q, k, v, delta, la, d_o=d_o)
+    tail = [x[-70:].contiguous() for x in (q, k, v, delta, la, d_o)]
+    assert torch.equal(got[-70:], cyfa.forward(*tail[:5]))
+    ref = cyfa.backward(*tail[:5], d_o=tail[5])
+    for name in ("dq", "dk", "dv", "d_delta", "d_log_alpha"):
+        assert torch.equal(grads[name][-70:], ref[name]), name
+
+
 def test_f32_forward_nan_stays_causal():
     """A NaN in v, k and q of one token reaches no earlier token's output."""
     cyfa = _cyfa()

@@ -18,7 +18,7 @@ fp64 CPU oracle timed on a bounded sample of the same workload on this host),
 prologue and epilogue kernels at the same shape), ``layer`` (prologue, forward
 and epilogue as three calls against the layer forward cyfa_forward_mixer) and
 ``paper_op`` (the forward at the paper's operator-benchmark shape, B 32, T 2048,
-H 4, d 256, and the vector-ALU backward there), ``wide`` (the forward with
+H 4, d 256, and the fp32 backward there), ``wide`` (the forward with
 m = 255 slots, 256 storage rows, at the 1.4B-scale layer shape, against the
 vector-ALU forward there) and ``narrow`` (the forward with m = 63 slots on 64
 storage rows at the same shape).
@@ -43,6 +43,8 @@ PEAK_BF16_TFLOPS = 2516.6       # MI355X dense bf16 MFMA (256 CU x 2.4 GHz x 409
 # library is built without them, so its vector-ALU kernels can issue at most one
 # fp32 FMA per lane per cycle: 256 CU x 2.4 GHz x 128 FLOP/clk.
 PEAK_F32_VALU_TFLOPS = 78.6
+# fp32 matrix instructions: 256 flop per CU and cycle (256 CUs, 2.4 GHz)
+PEAK_F32_MFMA_TFLOPS = 157.3
 M_ACTIVE = 127
 
 # Measured HBM bytes per launch of the fused 32-token kernel on the 1.4B-layer
@@ -293,7 +295,7 @@ def bwd_mfma_flops_per_token_head(d: int = 128, C: int = 32, R: int = 128) -> fl
 def backward_bench(args, torch, cyfa, w, prepared):
     """cyfa_backward on the benchmark workload (upstream gradient d_o ~ N(0, 1)): the
     matrix-core backward (bf16 with d = 128; the automatic choice there) and the
-    vector-ALU one on the same inputs."""
+    fp32 one on the same inputs."""
     dev = torch.device("cuda:0")
     scale, io_dtype, t = prepared
     g = torch.Generator(device=dev)
@@ -325,10 +327,10 @@ def backward_bench(args, torch, cyfa, w, prepared):
     ms_v = timed(cyfa.KERNEL_VALU, 10)
     flops_v = bwd_flops_per_token_head(w.dk, w.dv, w.m) * tokens * w.H
     tfl_v = flops_v / (ms_v * 1e-3) / 1e12
-    valu = dict(ms_per_step=ms_v, tokens_per_s=tokens / (ms_v * 1e-3), arithmetic="fp32 vector ALU",
+    valu = dict(ms_per_step=ms_v, tokens_per_s=tokens / (ms_v * 1e-3), arithmetic="fp32 matrix instructions",
                 alg_flops_per_step=flops_v,
-                roofline={"bound": "alu", "achieved": tfl_v, "peak": PEAK_F32_VALU_TFLOPS, "unit": "TFLOP/s",
-                          "frac": tfl_v / PEAK_F32_VALU_TFLOPS})
+                roofline={"bound": "mfma", "achieved": tfl_v, "peak": PEAK_F32_MFMA_TFLOPS, "unit": "TFLOP/s",
+                          "frac": tfl_v / PEAK_F32_MFMA_TFLOPS})
     if not (io_dtype == "bf16" and w.dk == 128 and w.dv == 128):
         return dict(workload=w.name, steps=10, **valu)
     steps = 20
@@ -634,7 +636,7 @@ def main():
     hbm = fb["bytes"] / ks / 1e9
     tfl = fb["flops"] / ks / 1e12
     if fb["kernel"] == "valu":
-        bound = "alu"               # fp32 vector-ALU arithmetic
+        bound = "alu"               # fp32 arithmetic: matrix instructions, the vector ALU for m > 127
     else:
         bound = "hbm" if fb["bytes"] / (PEAK_HBM_GBS * 1e9) >= fb["flops"] / (PEAK_BF16_TFLOPS * 1e12) \
             else "mfma"
@@ -642,7 +644,8 @@ def main():
             "launch_ms": fb["kernel_ms"],
             "traffic": measured_traffic(args.workload, fb["chunk"]) if fb["kernel"] == "mfma" else None}
     if bound == "alu":
-        roof.update(achieved=tfl, peak=PEAK_F32_VALU_TFLOPS, unit="TFLOP/s", frac=tfl / PEAK_F32_VALU_TFLOPS,
+        peak = PEAK_F32_VALU_TFLOPS if w.m > M_ACTIVE else PEAK_F32_MFMA_TFLOPS
+        roof.update(achieved=tfl, peak=peak, unit="TFLOP/s", frac=tfl / peak,
                     alg_flops_per_launch=fb["flops"])
     elif bound == "hbm":
         roof.update(achieved=hbm, peak=PEAK_HBM_GBS, unit="GB/s", frac=hbm / PEAK_HBM_GBS,

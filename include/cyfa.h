@@ -73,7 +73,7 @@ typedef enum {
 typedef enum {
     CYFA_KERNEL_AUTO = 0,  /* BF16 with d_k = d_v = 128 (m up to 255) or d_k =
                               d_v = 256 (m <= 127): matrix-core kernel; anything
-                              else: the vector-ALU kernel                     */
+                              else: as CYFA_KERNEL_VALU                       */
     CYFA_KERNEL_VALU = 1,  /* fp32 arithmetic, any supported shape and dtype: the
                               fp32 matrix instructions for m <= 127, the vector
                               ALU for m > 127 or with segments = 1             */
@@ -95,7 +95,8 @@ typedef enum {
  *                it beyond rounding (App. B: the chunk form is exact).
  *   segments     sequence segments per (b, h) run in parallel: 0 = automatic,
  *                else 1..1024 (the VALU kernel: groups of 16-token chunks, more
- *                than one only for d_k, d_v <= 128 and m <= 127; the MFMA kernel
+ *                than one only for d_k, d_v <= 128 and m <= 127, where the count
+ *                itself is without effect; the MFMA kernel
  *                at m > 127 and, with d = 128, at m <= 63: groups of 32-token
  *                chunks).  The state entering a
  *                segment is obtained from a pre-pass over the earlier segments.

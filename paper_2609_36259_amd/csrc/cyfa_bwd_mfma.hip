@@ -1,12 +1,12 @@
 // Matrix-core (bf16 MFMA) backward of the chunk-wise CyFA forward: bf16 inputs,
 // d_k = d_v = 128, m <= 127, 32-token chunks.
 //
-// The gradients are those of the vector-ALU backward (reverse mode of the
+// The gradients are those of the fp32 backward (reverse mode of the
 // absolute-clock recurrence and readout, Sec. 3.2 Eqs. cyfa-absolute-recurrence
 // and cyfa-absolute-readout, chunk by chunk as in App. B; the clock increments
 // receive the reverse cumulative sum of the per-token clock gradients, Eq.
 // app-clock-gradient-accumulation; the per-token formulas are written out at
-// the top of cyfa_bwd_valu.hip).  Here every dense product runs on bf16
+// the top of cyfa_bwd_f32.hip).  Here every dense product runs on bf16
 // matrix-core tiles with fp32 accumulation, and the states stay in MFMA
 // accumulators while a workgroup walks its chunk group:
 //   (1) fwd_contrib_kernel (b, h, group): the group's own contribution to the
@@ -29,7 +29,7 @@
 //       from da the gradient of beta and the clock gradient of the write a_t, and
 //       dL/dG.  The first group ends at the sequence start: dK0, dV0.
 // The reverse cumulative sums (dlog_alpha, ddelta, dclock0) and dR = dM Phi^T
-// are the vector-ALU backward's last two kernels (launch_bwd_tail).
+// are the last two kernels of either backward (launch_bwd_tail).
 //
 // Within a chunk (token rows r, s; G_r the chunk-local inclusive sum of log
 // alpha; gamma_r = exp(G_r); rho_s = exp(G_C - G_s); Gamma_rs = exp(G_r - G_s)
@@ -634,18 +634,28 @@ __device__ __forceinline__ double block_token_sum(const float *x, int stride, in
 // 2 (w8 / 4) + 1 of both states (two waves per SIMD: the chunk loop waits on LDS and
 // global loads, which the second wave covers).  The last group's contribution is
 // never read (no walk starts after it), so its workgroups form only its clock entry
-// and total log decay.
+// and total log decay.  Extra blocks form the readout matrix on the compute units that
+// those leave (a launch of its own before this one took 8.5 us).
+constexpr int kPrepBlkRows = 16;
 struct CLay {
     static constexpr int K = 0, V = kT32, A = 2 * kT32, SC = 3 * kT32, RED = SC + kScBytes;
     static constexpr int BYTES = RED + kNT8 / 64 * 8;
 };
-__global__ __launch_bounds__(kNT8, 1) void fwd_contrib_kernel(Args a) {
+__global__ __launch_bounds__(kNT8, 1) void fwd_contrib_kernel(Args a, float mz_scale) {
     using L = CLay;
     __shared__ __attribute__((aligned(256))) char smem[L::BYTES];
+    static_assert(prep_lds_bytes(kPrepBlkRows) <= L::BYTES, "readout-matrix blocks fit");
     const BwdParams &p = a.p;
-    const int bh = blockIdx.x, g = blockIdx.y, b = bh / p.H, h = bh % p.H;
+    const int BH = p.B * p.H, bh = blockIdx.x % BH, g = blockIdx.x / BH, b = bh / p.H, h = bh % p.H;
     const int tid = threadIdx.x, lane = tid & 63, w8 = tid >> 6, wi = w8 & 3, xh = w8 >> 2;
     const int m = p.m;
+    if (g >= p.groups) {
+        constexpr int kPer = kStoreRows / kPrepBlkRows;
+        const int u = blockIdx.x - BH * p.groups;
+        readout_prep_rows<kPrepBlkRows, kNT8>(m, p.R, nullptr, const_cast<__bf16 *>(a.Mz), mz_scale, u / kPer, u % kPer,
+                                              tid, smem);
+        return;
+    }
     const int Tb = tokens_of(p, b);
     const int c_begin = g * p.cpg, c_end = min(c_begin + p.cpg, p.nc);
     Sc &sc = *lds_at<Sc>(smem, L::SC);
@@ -1422,14 +1432,13 @@ hipError_t launch_bwd_mfma(BwdParams p, void *ws, hipStream_t s) {
     p.dMp = reinterpret_cast<float *>(take(BH * G * 128 * 128 * 4));
     p.fin = reinterpret_cast<double *>(take(BH * kCombBlocks * 8));
     a.p = p;
-    hipError_t e = launch_readout_prep(p.H, p.m, p.R, nullptr, Mz, p.scale * 1.4426950408889634f, s);
-    if (e != hipSuccess) return e;
     const dim3 block(kNT), grp(BH, G);
-    hipLaunchKernelGGL(fwd_contrib_kernel, grp, dim3(kNT8), 0, s, a);
+    hipLaunchKernelGGL(fwd_contrib_kernel, dim3(BH * G + p.H * (kStoreRows / kPrepBlkRows)), dim3(kNT8), 0, s, a,
+                       p.scale * 1.4426950408889634f);
     hipLaunchKernelGGL(readout_kernel, grp, block, 0, s, a);
     hipLaunchKernelGGL(adj_contrib_kernel, grp, dim3(kNT8), 0, s, a);
     hipLaunchKernelGGL(grad_kernel, grp, dim3(kNT8), 0, s, a);
-    e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_bwd_tail(p, p.B * p.groups, s);
 }

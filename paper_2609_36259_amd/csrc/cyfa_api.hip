@@ -448,6 +448,7 @@ cyfa_status cyfa_forward_mixer(const cyfa_fwd_desc *desc, const cyfa_mixer_weigh
         mp.q_in = q_in; mp.k_in = k_in; mp.v_in = v_in;
         mp.wq = mw->conv_q; mp.wk = mw->conv_k; mp.wv = mw->conv_v; mp.gq = mw->norm_q; mp.gk = mw->norm_k;
         mp.lens = lens;
+        mp.resident = true;
         mp.q_out = buf; mp.k_out = buf + one; mp.v_out = buf + 2 * one;
         delta = reinterpret_cast<float *>(buf + 3 * one);
         mp.z_delta = mw->z_delta; mp.b_delta = mw->b_delta; mp.delta = delta;

@@ -20,6 +20,7 @@ struct MixParams {
     const int *lens;
     void *q_out, *k_out, *v_out;
     float *delta, *log_alpha, *beta;
+    bool resident;                  // ordinary stores: the next launch reads the outputs back
 };
 
 // Gate activations of the prologue (Eq. clock_gradient_stabilization and the

@@ -731,28 +731,18 @@ __global__ __launch_bounds__(kNT, 1) void wide_forward_kernel(WideArgs a) {
 // amplitude from the scanning lane), and after one barrier updates its state blocks
 // from the shared tiles.  The last group's contribution is never read, so its
 // workgroup copies (K0, V0) for the forward's prologues instead and forms only its
-// total log decay.  Extra blocks after the contributions' form the readout matrix: the
-// last group's workgroups end early and leave them their compute units (B 4, T 4096, H 16:
-// this launch 63 -> 82 us, but the 23 us one before it is gone: 541 -> 537 us per call).
+// total log decay.
 constexpr int kCS = 64;                             // tokens per step
-constexpr int kPrepBlocks = kR / (kNT / 256 * kWideRowsPerBlock);   // readout-matrix blocks per head
-__global__ __launch_bounds__(kNT, 1) void wide_contrib_kernel(WideArgs a, float mz_scale) {
+__global__ __launch_bounds__(kNT, 1) void wide_contrib_kernel(WideArgs a) {
     constexpr int TK = kCS * PSB;                   // [64][128] tile
     constexpr int TA = kCS * PWB;                   // [64][256] tile
     __shared__ __attribute__((aligned(256))) char smem[2 * TK + TA];
     __shared__ double red[kNT / 64];
-    static_assert(prep_wide_lds_bytes(kNT) <= 2 * TK + TA, "readout-matrix blocks fit");
     const FwdParams &p = a.p;
-    const int BH = p.B * p.H, bh = blockIdx.x % BH, g = blockIdx.x / BH, b = bh / p.H, h = bh % p.H;
+    const int bh = blockIdx.x, g = blockIdx.y, b = bh / p.H, h = bh % p.H;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int hh = w >> 2, cb = w & 3;
     const int m = p.m;
-    if (g >= a.groups) {
-        const int u = blockIdx.x - BH * a.groups;
-        readout_prep_wide_rows<kNT>(m, p.R, nullptr, const_cast<__bf16 *>(a.Mz), const_cast<__bf16 *>(a.MzT), mz_scale,
-                                    u / kPrepBlocks, u % kPrepBlocks, tid, smem);
-        return;
-    }
     const int Tb = seq_tokens(p, b);
     const size_t row0 = seq_row0(p, b);
     const int t_begin = min(g * a.cpg * kC, Tb), t_end = min((g + 1) * a.cpg * kC, Tb);
@@ -952,18 +942,14 @@ hipError_t launch_fwd_mfma_wide(const FwdParams &p, int groups, void *ws, hipStr
         a.gclk = reinterpret_cast<double *>(base + L.gclk);
         a.S0 = reinterpret_cast<float *>(base + L.s0);
     }
-    const float mz_scale = p.scale * 1.4426950408889634f;
-    const dim3 grid(p.B * p.H, a.groups);
-    hipError_t e;
-    if (a.groups > 1) {
-        hipLaunchKernelGGL(wide_contrib_kernel, dim3(p.B * p.H * a.groups + p.H * kPrepBlocks), dim3(kNT), 0, st, a,
-                           mz_scale);
-        e = hipGetLastError();
-    } else {
-        e = launch_readout_prep_wide_bf16(p.H, p.m, p.R, const_cast<__bf16 *>(a.Mz), const_cast<__bf16 *>(a.MzT),
-                                          mz_scale, st);
-    }
+    hipError_t e = launch_readout_prep_wide_bf16(p.H, p.m, p.R, const_cast<__bf16 *>(a.Mz),
+                                                 const_cast<__bf16 *>(a.MzT), p.scale * 1.4426950408889634f, st);
     if (e != hipSuccess) return e;
+    const dim3 grid(p.B * p.H, a.groups);
+    if (a.groups > 1) {
+        hipLaunchKernelGGL(wide_contrib_kernel, grid, dim3(kNT), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     hipExtLaunchKernelGGL(wide_forward_kernel, grid, dim3(kNT), 0, st, ev_start, ev_stop, 0, a);
     return hipGetLastError();
 }

@@ -46,7 +46,8 @@ struct F32Ws {
     float *Kst, *Vst;               // [BH][nc] 4 x d/32 blocks [channel][basis] of the states entering each chunk
     float *DKe, *DVe;               // the same of the adjoint states at each chunk's end
     float *Ko, *Vo;                 // final states and clocks of a forward call, or NULL
-    double *clko;
+    double *clko;                   // (may be p.clock0)
+    double *clkT;                   // [BH] clock after the last token, or NULL
 };                                  // (BwdParams::U and dP: [BH][Tpad/32] 4 blocks [token][basis])
 
 // ---------------------------------------------------------------------------
@@ -151,7 +152,9 @@ __global__ __launch_bounds__(256) void f32_prep_kernel(BwdParams p, F32Ws w) {
             if (c0 + lane < p.nc) cl[c0 + lane] = reduce_clock(base + (s - x), m);
             base = reduce_clock(base + mfma::lane63(s), m);
         }
-        if (w.clko && lane == 0) w.clko[bh] = base;
+        // clock_out may be clock0, which the table blocks of this launch still read, so that the
+        // states' launch copies it there
+        if (w.clkT && lane == 0) w.clkT[bh] = base;
         return;
     }
     const int h = blockIdx.x / (kR / kPrepRows), i0 = (blockIdx.x % (kR / kPrepRows)) * kPrepRows;
@@ -327,10 +330,16 @@ __device__ __forceinline__ void state_columns(const BwdParams &p, const F32Ws &w
     }
 }
 
+// clock_out, from a sequence's first workgroup of a launch after the tables'
+__device__ __forceinline__ void clock_to_caller(const F32Ws &w, int bh) {
+    if (w.clko && blockIdx.y == 0 && threadIdx.x == 0) w.clko[bh] = w.clkT[bh];
+}
+
 template <int DK, int DV, typename Tin, bool ADJ, bool WALK>
 __global__ __launch_bounds__(256, 4) void f32_states_kernel(BwdParams p, F32Ws w) {
     __shared__ __attribute__((aligned(16))) float lds[kTC * kLS + kTC + 4 * kLdsTile];
     const int y = blockIdx.y;
+    if (WALK && !ADJ) clock_to_caller(w, blockIdx.x);
     if (y < DK / 64)
         state_columns<DK, Tin, ADJ, WALK>(p, w, ADJ ? p.q : p.k, ADJ ? p.dP : w.cs, ADJ ? w.DKe : w.Kst,
                                           ADJ ? p.dK_T : p.K0, p.dK_T, ADJ ? p.gK0 : w.Ko, y, lds);
@@ -350,6 +359,7 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
     const int bh = blockIdx.x, tid = threadIdx.x, m = p.m, nc = p.nc;
     const float *ge = w.gend + (size_t)bh * nc;
     double fin = 0.0;
+    if (!ADJ) clock_to_caller(w, bh);
     auto run = [&](int D, float *slots, const float *ext, const float *fext, float *gext) {
         const size_t st = (size_t)kR * D / 4;
         for (int e = (blockIdx.y % kHalf) * 256 + tid; e < kR * D / 4; e += 256 * kHalf) {

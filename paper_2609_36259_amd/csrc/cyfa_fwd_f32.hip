@@ -210,7 +210,7 @@ hipError_t launch_dv(const BwdParams &p, const F32Ws &w, void *out, float *logit
 
 size_t fwd_f32_workspace_bytes(const FwdParams &f) {
     const size_t BH = (size_t)f.B * f.H, nc = ((size_t)f.T + kTC - 1) / kTC, Tpad = nc * kTC;
-    return align_up(2 * readout_f32_bytes(f.H)) + align_up(BH * nc * 8) + align_up(BH * Tpad * kR * 4) +
+    return align_up(2 * readout_f32_bytes(f.H)) + align_up(BH * nc * 8) + align_up(BH * 8) + align_up(BH * Tpad * kR * 4) +
            align_up(BH * Tpad * 8) + align_up(3 * BH * Tpad * 4) + align_up(BH * nc * 4) +
            align_up(BH * nc * kR * f.dk * 4) + align_up(BH * nc * kR * f.dv * 4);
 }
@@ -231,6 +231,7 @@ hipError_t launch_fwd_f32(const FwdParams &f, void *ws, hipStream_t s) {
     w.Mi = take(2 * readout_f32_bytes(p.H));
     w.MiT = w.Mi + (size_t)p.H * kR * kR;
     w.clk = reinterpret_cast<double *>(take(BH * nc * 8));
+    w.clkT = reinterpret_cast<double *>(take(BH * 8));
     w.cs = take(BH * Tpad * kR * 4);
     w.G = reinterpret_cast<double *>(take(BH * Tpad * 8));
     w.gam = take(3 * BH * Tpad * 4);

@@ -406,6 +406,29 @@ def test_f32_more_sequences_than_a_grid_axis():
         assert torch.equal(grads[name][-70:], ref[name]), name
 
 
+@pytest.mark.parametrize("B,T,H", [(8, 2048, 16), (1, 4200, 2)])
+def test_f32_resume_in_place_with_more_blocks_than_the_chip_holds(B, T, H):
+    """clock_out over clock0, K_out over K0 and V_out over V0 with 4096 table blocks (twice
+    what is resident at a time: the later ones start after the sequences' final clocks are
+    known), and with more than 64 chunks (the tables' own launch): bit for bit the call with
+    separate outputs."""
+    cyfa = _cyfa()
+    d, g = 64, torch.Generator(device="cuda")
+    g.manual_seed(T)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=g)  # noqa: E731
+    q, k, v = (rnd(B, T, H, d) / 8 for _ in range(3))
+    delta, la = torch.rand((B, T, H), device="cuda", generator=g), -0.1 * rnd(B, T, H).abs()
+    K, V = rnd(B, H, 128, d), rnd(B, H, 128, d)
+    K[:, :, 127:] = 0
+    V[:, :, 127:] = 0
+    clock = 127 * torch.rand((B, H), device="cuda", dtype=torch.float64, generator=g)
+    ref = cyfa.forward(q, k, v, delta, la, K0=K.clone(), V0=V.clone(), clock0=clock.clone(), return_state=True)
+    assert (ref["clock"] - clock).abs().min() > 1e-3
+    got = cyfa.forward(q, k, v, delta, la, K0=K, V0=V, clock0=clock, K_out=K, V_out=V, clock_out=clock)
+    assert torch.equal(got["o"], ref["o"])
+    assert torch.equal(K, ref["K"]) and torch.equal(V, ref["V"]) and torch.equal(clock, ref["clock"])
+
+
 def test_f32_forward_nan_stays_causal():
     """A NaN in v, k and q of one token reaches no earlier token's output."""
     cyfa = _cyfa()

@@ -446,6 +446,27 @@ def test_f32_forward_nan_stays_causal():
             assert torch.isnan(o[0, at, 0]).any(), (name, at)
 
 
+@pytest.mark.parametrize("name", ["delta", "beta", "log_alpha"])
+def test_f32_forward_nonfinite_gates_stay_causal(name):
+    """A NaN or infinity in a gate of one token, inside and at the edges of the 32-token
+    tiles and 64-token chunks, reaches no earlier token, and the token itself is not finite
+    (alpha = 0 aside, whose decay from the token to itself is a matter of definition)."""
+    cyfa = _cyfa()
+    x = make_forward_inputs(1, 96, 1, 64, 64, seed=313, dtype="f32")
+    t = upload(x)
+    run = lambda **kw: cyfa.forward(*(kw.get(n, t[n]) for n in ("q", "k", "v", "delta", "log_alpha", "beta", "R")),  # noqa: E731
+                                    scale=x["scale"])
+    clean = run()
+    for value in (float("nan"), float("inf"), float("-inf")):
+        for at in (5, 31, 32, 40, 63, 64, 77):
+            bad = t[name].clone()
+            bad[0, at, 0] = value
+            o = run(**{name: bad})
+            assert (o[:, :at] - clean[:, :at]).abs().max() < 1e-5, (value, at)
+            if not (name == "log_alpha" and value < 0):
+                assert not torch.isfinite(o[0, at, 0]).any(), (value, at)
+
+
 @pytest.mark.parametrize("m", [3, 65, 127])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_decode_both_readout_routes(m, dtype):

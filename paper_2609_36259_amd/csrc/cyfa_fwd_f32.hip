@@ -81,15 +81,15 @@ __global__ __launch_bounds__(256, 2) void f32_forward_kernel(BwdParams p, F32Ws 
     __syncthreads();
     f32x16 own = {};
     for (int sb = 0; sb <= tb; ++sb) {
-        f32x16 s = ld_block(part + sb * 1024 + lane4) + ld_block(part + (sb + 2) * 1024 + lane4);
-        // beta goes to the masked scores, and a phase that is NaN (a non-finite delta) enters as
-        // -1: tokens t < s have a zero score, which the product would multiply by the NaN.  The
-        // tokens t >= s get it from their score (beta) or from their own phases (delta).
-        s = causal(s, Gt, w.G + row0 + 32 * sb + 4 * h, w.bet + row0 + 32 * sb + 4 * h, tl, 32 * sb, h);
+        // A phase that is NaN (a non-finite delta) enters as -1, and beta goes to the masked
+        // scores: tokens t < s have a zero score, which the product would multiply by the NaN.
+        // The tokens t >= s get it from their own phases (delta) or their score (beta).
         f32x16 a = swp.template swap<false>(ld_block(cs + (4 * sb + wv) * 1024));
 #pragma unroll
-        for (int r = 0; r < 16; ++r) a[r] = fmaxf(a[r], -1.f);
-        mma_step(own, a * wc.at(32 * wv + l31), s);
+        for (int r = 0; r < 16; ++r) a[r] = fmaxf(a[r], -1.f) * wc.at(32 * wv + l31);
+        f32x16 s = ld_block(part + sb * 1024 + lane4) + ld_block(part + (sb + 2) * 1024 + lane4);
+        s = causal(s, Gt, w.G + row0 + 32 * sb + 4 * h, w.bet + row0 + 32 * sb + 4 * h, tl, 32 * sb, h);
+        mma_step(own, a, s);
     }
     const f32x16 ph = ld_block(cs + (4 * tb + wv) * 1024);
     st_block(xs + wv * 1024 + lane4, rotate_block(acc * g + own, ph, 1.f, p.scale));

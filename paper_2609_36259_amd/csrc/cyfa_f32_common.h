@@ -48,6 +48,7 @@ struct F32Ws {
     float *Ko, *Vo;                 // final states and clocks of a forward call, or NULL
     double *clko;                   // (may be p.clock0)
     double *clkT;                   // [BH] clock after the last token, or NULL
+    int c0;                         // first chunk of a launch with the chunks on the grid's z axis
 };                                  // (BwdParams::U and dP: [BH][Tpad/32] 4 blocks [token][basis])
 
 // ---------------------------------------------------------------------------
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(256) void f32_prep_kernel(BwdParams p, F32Ws w) {
 // do_t^T, chunks in reverse), 64 columns of a state per workgroup, wave w rows 32 w ..
 // + 31.  The columns of a state are independent, so with enough sequences (WALK) one
 // workgroup carries its columns through every chunk and no combine is needed; with
-// few, every chunk's own contribution is formed in parallel (one per blockIdx.z) and
+// few, every chunk's own contribution is formed in parallel (chunk c0 + blockIdx.z) and
 // f32_scan_kernel combines them.  The line lies at 256 workgroups, one per compute
 // unit: a walk's step is a dependent chain of two memory round trips.
 template <int D, typename Tin, bool ADJ, bool WALK>
@@ -242,7 +243,7 @@ __device__ __forceinline__ void state_columns(const BwdParams &p, const F32Ws &w
     u32x4 tok4[NQ];
     f32x16 a[2];
     float fac = 0.f;
-    auto chunk_of = [&](int it) { return WALK ? (ADJ ? p.nc - 1 - it : it) : (int)blockIdx.z; };
+    auto chunk_of = [&](int it) { return WALK ? (ADJ ? p.nc - 1 - it : it) : w.c0 + (int)blockIdx.z; };
     auto fetch_tok = [&](int it) {
         const int c = chunk_of(it);
         const TokRows<Tin> tr(tok, first_row(p, b) + c * kTC, hd, p.H, D, min(Tb - c * kTC, kTC));
@@ -415,19 +416,21 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
 }
 
 template <int DK, int DV, typename Tin, bool ADJ>
-void launch_states(const BwdParams &p, const F32Ws &w, hipStream_t s) {
+void launch_states(const BwdParams &p, F32Ws w, hipStream_t s) {
     const int BH = p.B * p.H, ny = (DK + DV) / 64;
     if (BH * ny >= 256) {
         hipLaunchKernelGGL((f32_states_kernel<DK, DV, Tin, ADJ, true>), dim3(BH, ny), dim3(256), 0, s, p, w);
         return;
     }
-    if (p.nc > 0)
-        hipLaunchKernelGGL((f32_states_kernel<DK, DV, Tin, ADJ, false>), dim3(BH, ny, p.nc), dim3(256), 0, s, p, w);
+    // (a grid's z axis holds 65535 blocks)
+    for (w.c0 = 0; w.c0 < p.nc; w.c0 += 65535)
+        hipLaunchKernelGGL((f32_states_kernel<DK, DV, Tin, ADJ, false>), dim3(BH, ny, min(p.nc - w.c0, 65535)), dim3(256), 0,
+                           s, p, w);
     hipLaunchKernelGGL((f32_scan_kernel<DK, DV, ADJ>), dim3(BH, kBwdFinParts), dim3(256), 0, s, p, w);
 }
 
-// (chunk, sequence) grids here are flat: a grid's y and z hold 65535 blocks only, and a batch
-// may have more sequences.
+// The (chunk, sequence) grids of the tables are flat: a grid's y and z hold 65535 blocks
+// only, and a batch may have more sequences.
 inline void launch_front(const BwdParams &p, const F32Ws &w, hipStream_t s) {
     const int BH = p.B * p.H, base = p.H * (kR / kPrepRows) + BH;
     const bool one = p.nc <= kTableChunks;

@@ -406,6 +406,24 @@ def test_f32_more_sequences_than_a_grid_axis():
         assert torch.equal(grads[name][-70:], ref[name]), name
 
 
+def test_f32_more_chunks_than_a_grid_axis():
+    """One sequence of 65537 64-token chunks (a grid's third axis holds 65535): against the
+    same tokens in two calls, the second from the first's state.  Two fp32 evaluations with
+    the same chunks: 1e-5."""
+    cyfa = _cyfa()
+    T, d, half = 64 * 65536 + 3, 64, 64 * 32768
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    q, k, v = (torch.randn((1, T, 1, d), device="cuda", generator=g) for _ in range(3))
+    delta, la = torch.rand((1, T, 1), device="cuda", generator=g), -torch.rand((1, T, 1), device="cuda", generator=g)
+    got = cyfa.forward(q, k, v, delta, la, return_state=True)
+    a = cyfa.forward(*(x[:, :half].contiguous() for x in (q, k, v, delta, la)), return_state=True)
+    b = cyfa.forward(*(x[:, half:].contiguous() for x in (q, k, v, delta, la)), K0=a["K"], V0=a["V"], clock0=a["clock"],
+                     return_state=True)
+    for x, y in ((got["o"][:, :half], a["o"]), (got["o"][:, half:], b["o"]), (got["K"], b["K"]), (got["V"], b["V"])):
+        assert (x - y).abs().max() <= 1e-5 * y.abs().max()
+
+
 @pytest.mark.parametrize("B,T,H", [(8, 2048, 16), (1, 4200, 2)])
 def test_f32_resume_in_place_with_more_blocks_than_the_chip_holds(B, T, H):
     """clock_out over clock0, K_out over K0 and V_out over V0 with 4096 table blocks (twice

@@ -1456,16 +1456,22 @@ hipError_t launch_fwd_mfma(const FwdParams &p, int P, void *ws, hipStream_t st,
     a.zero_init = (p.K0 || p.V0) ? 0 : 1;
     a.hv = virtual_heads(p);
     if (mix) a.mix = *mix;
+    const int BHv = p.B * p.H * a.hv;
     // With two to four segments and no initial state, each segment's workgroup sums the
     // earlier contributions in its prologue and the scan between the pre-pass and the
-    // fused kernel (14 .. 16 us) is saved: B 32, T 2048, H 4, d 256 (two segments) 273 ->
-    // 264 us, B 8, T 2048, H 16, d 128 (four) 161 -> 155 us.  A contribution costs the last
+    // fused kernel is saved: B 32, T 2048, H 4, d 256 (two segments) 273 -> 264 us, B 8,
+    // T 2048, H 16, d 128 (four) 161 -> 155 us.  A contribution costs the last
     // segment's workgroup about 4 us: with eight segments the call took 176 us against 166.
+    // The scan takes 14 .. 16 us at 128 sequences but 5 at 16, which three contributions
+    // (or two, where a segment is one chunk, with little else to wait for) exceed: four
+    // segments at T 100, time with the scan over time without, 0.83 at 8 sequences of 128
+    // channels, 0.89 at 32, 0.97 at 64, 1.05 at 96, 1.10 at 128; three of one chunk 0.90, 0.93,
+    // 1.02, 1.08, 1.04; three of several 1.02 .. 1.05 and two 1.00 .. 1.15 at 8 .. 64.
     // Initial states add one more to every workgroup (B 16, T <= 1024, packed, H 16, two
     // segments: 212 against 203 us) and stay with the scan.  The pre-pass then sums the
     // increments before its segment itself, which the bound on T keeps short.
-    a.direct = a.P > 1 && a.P <= 4 && a.zero_init && a.nchunks > 0 && p.T <= 8192;
-    const int BHv = p.B * p.H * a.hv;
+    a.direct = a.P > 1 && a.P <= 4 && a.zero_init && a.nchunks > 0 && p.T <= 8192 &&
+               (a.P == 2 || (a.P == 3 && a.cps > 1) || BHv >= 96);
 
     hipError_t e = launch_cc<32>(a, BHv, st, ev_start, ev_stop);
     if (e != hipSuccess) return e;

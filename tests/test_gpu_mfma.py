@@ -276,3 +276,28 @@ def test_entering_states_without_a_scan(d, H, segments):
             assert rel_err(a[key][i].cpu(), b[key][i].cpu()) <= TOL_BF16, (key, i, n)
     dc = torch.remainder(a["clock"] - b["clock"], x["m"])
     assert torch.minimum(dc, x["m"] - dc).max() <= 1e-9
+
+
+@pytest.mark.parametrize("B,T,H,d,segments", [
+    (32, 90, 3, 128, 3), (31, 90, 3, 128, 3),        # one-chunk segments, 96 sequences and 93
+    (12, 350, 8, 128, 4), (16, 128, 3, 256, 4),      # four segments, 96 sequences of 128 channels
+])
+def test_entering_states_of_many_sequences(B, T, H, d, segments):
+    """Three one-chunk segments and four segments sum the earlier contributions in the fused
+    kernel from 96 sequences (of 128 channels) on, and take the scan below: against the fp32
+    forward, with lengths that end in every segment."""
+    cyfa = _cyfa()
+    x = make_forward_inputs(B, T, H, d, d, seed=130 + B, dtype="bf16")
+    t = upload(x)
+    n = [(T, 0, 1, T // 2, T // 3 + 3, T - 1)[b % 6] for b in range(B)]
+    lens = torch.tensor(n, dtype=torch.int32, device="cuda")
+    run = lambda **kw: cyfa.forward(t["q"], t["k"], t["v"], t["delta"], t["log_alpha"], t["beta"], t["R"],  # noqa: E731
+                                    scale=x["scale"], lens=lens, return_state=True, **kw)
+    a, b = run(kernel=cyfa.KERNEL_MFMA, segments=segments), run(kernel=cyfa.KERNEL_VALU)
+    live = lambda o: torch.cat([o[i, :k] for i, k in enumerate(n)]).float().cpu()  # noqa: E731
+    assert rel_err(live(a["o"]), live(b["o"])) <= TOL_BF16
+    for key in ("K", "V"):
+        for i, k in enumerate(n):
+            assert rel_err(a[key][i].cpu(), b[key][i].cpu()) <= TOL_BF16, (key, i, k)
+    dc = torch.remainder(a["clock"] - b["clock"], x["m"])
+    assert torch.minimum(dc, x["m"] - dc).max() <= 1e-9

@@ -10,7 +10,6 @@
 #pragma once
 
 #include "cyfa_internal.h"
-#include "cyfa_rows.h"
 
 namespace cyfa {
 
@@ -87,78 +86,6 @@ __device__ __forceinline__ void readout_prep_rows(int m, const float *__restrict
             Mz[((size_t)h * kStoreRows + i) * kStoreRows + jint] = (__bf16)z;
         }
     }
-}
-
-// ---- 256 storage rows (127 < m <= 255) ----
-// A block of NT = 256 or 512 threads (a kernel of its own, or extra blocks of the m > 127
-// contribution launch), LDS from the caller (16-byte aligned): the threads j + 256 g form
-// rows 8 (NT/256 rb + g) .. + 7 of M_h, thread j column j of them,
-// M[i][j] = sum_s R[i][s] Phi[s][j], with Phi[s][j] from a table of the m angles
-// 2 pi n / m (index l s mod m for frequency l = (j + 1) / 2), four
-// terms per step from 16-byte reads of R's staged rows.  Writes the fp32 M (paper
-// basis order) and/or, for the matrix-core kernel, Mz = zs M in its internal basis
-// order (pair j at 2j-2, 2j-1, DC at 254, padding 255; kMaskLogit in the padding
-// column of inactive slots) and its transpose MzT, each when non-null.
-constexpr int kWideRowsPerBlock = 8;
-typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
-__host__ __device__ constexpr int prep_wide_lds_bytes(int nt) {
-    return (2 + nt / 256 * kWideRowsPerBlock) * kWideRows * 4;
-}
-template <int NT>
-__device__ __forceinline__ void readout_prep_wide_rows(int m, const float *__restrict__ R, float *__restrict__ M,
-                                                       __bf16 *__restrict__ Mz, __bf16 *__restrict__ MzT, float zs,
-                                                       int h, int rb, int tid, char *lds) {
-    float *tab = reinterpret_cast<float *>(lds);            // [2][256] cos, sin of 2 pi r / m
-    const int j = tid & 255, i0 = (NT / 256 * rb + (tid >> 8)) * kWideRowsPerBlock;
-    float *Rr = tab + (2 + (tid >> 8) * kWideRowsPerBlock) * kWideRows;     // [8][256]
-    if (tid < m) {
-        double sn, cs;
-        sincospi(2.0 * (double)j / (double)m, &sn, &cs);
-        tab[j] = (float)cs;
-        tab[kWideRows + j] = (float)sn;
-    }
-    const float *Rh = R ? R + (size_t)h * m * m : nullptr;
-    for (int r = 0; r < kWideRowsPerBlock; ++r) {
-        const int i = i0 + r;
-        Rr[r * kWideRows + j] = (i < m && j < m) ? (Rh ? Rh[(size_t)i * m + j] : (i == j ? 1.f : 0.f)) : 0.f;
-    }
-    __syncthreads();
-    float acc[kWideRowsPerBlock];
-#pragma unroll
-    for (int r = 0; r < kWideRowsPerBlock; ++r) acc[r] = 0.f;
-    if (j < m) {
-        const int l = (j + 1) >> 1;
-        const float *t = (j == 0 || (j & 1)) ? tab : tab + kWideRows;
-        int idx = 0;
-        // R's staged rows are zero past column m, so the steps may run to a multiple of 4
-        for (int s0 = 0; s0 < m; s0 += 4) {
-            float ph[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                ph[q] = t[idx];
-                idx += l;
-                if (idx >= m) idx -= m;
-            }
-#pragma unroll
-            for (int r = 0; r < kWideRowsPerBlock; ++r) {
-                const float4 rv = *reinterpret_cast<const float4 *>(Rr + r * kWideRows + s0);
-                acc[r] = fmaf(rv.x, ph[0], fmaf(rv.y, ph[1], fmaf(rv.z, ph[2], fmaf(rv.w, ph[3], acc[r]))));
-            }
-        }
-    }
-    const float cscale = j == 0 ? (float)(1.0 / sqrt((double)m)) : (float)sqrt(2.0 / (double)m);
-    const int jint = j == 0 ? kWideRows - 2 : (j == kWideRows - 1 ? kWideRows - 1 : j - 1);
-    bf16v8 col;
-#pragma unroll
-    for (int r = 0; r < kWideRowsPerBlock; ++r) {
-        const int i = i0 + r;
-        const float val = (j < m && i < m) ? acc[r] * cscale : 0.f;
-        if (M) M[((size_t)h * kWideRows + i) * kWideRows + j] = val;
-        const float zv = (j == kWideRows - 1 && i >= m) ? kMaskLogit : zs * val;
-        col[r] = (__bf16)zv;
-        if (Mz) Mz[((size_t)h * kWideRows + i) * kWideRows + jint] = col[r];
-    }
-    if (MzT) *reinterpret_cast<bf16v8 *>(MzT + ((size_t)h * kWideRows + jint) * kWideRows + i0) = col;
 }
 
 }  // namespace cyfa

@@ -34,17 +34,18 @@
 //   da = (Q K^T (.) Gamma)^T dP + rho (.) K DK'^T + (dO V^T (.) Gamma)^T U + rho (.) V DV'^T
 // Every product is a chain of 32 x 32 x 2 fp32 tiles with the tokens on the lanes
 // (cyfa_tile_f32.h): one wave takes 32 tokens from their score tile to u and dp
-// with every intermediate in registers.  fp32 throughout, as the vector-ALU kernels
-// that these replace: 27.3 -> 3.6 ms at B 32, T 2048, H 4, d_k = d_v = 256 (bf16 inputs;
-// 330 GFLOP in tiles, 91 TFLOP/s of the 157 the fp32 matrix instructions have) and 574
-// -> 283 us at B 4, T 1000, H 4, d = 64 (fp32).  The readout and gradient kernels run one
-// wave per SIMD (a wave's tokens need 4 .. 5 tiles of 64 registers) and are bound by
-// their matrix instructions, the vector work between them and the loads' latency at
-// each product's start.  Kernels: (0) clocks and phase tables; (1)
+// with every intermediate in registers.  fp32 throughout: 27.3 -> 3.6 ms at B 32, T 2048,
+// H 4, d_k = d_v = 256 (bf16 inputs; 330 GFLOP in tiles, 91 TFLOP/s of the 157 the fp32
+// matrix instructions have) against vector-ALU kernels on 16-token chunks.  The readout and
+// gradient kernels run one wave per SIMD (a wave's tokens need 4 .. 5 tiles of 64
+// registers) and are bound by their matrix instructions, the vector work between them and
+// the loads' latency at each product's start.  Short calls, where that chain of one wave is
+// all the time, have kernels of their own for (2) and (4) (cyfa_bwd_f32_short.h).  Kernels:
+// (0) clocks and phase tables; (1)
 // states entering every chunk; (2) readout recomputation and its adjoint; (3)
 // adjoint states at every chunk's end; (4) token gradients; (5) reverse cumulative
 // sums, per sequence; (6) dR, per head.
-#include "cyfa_f32_common.h"
+#include "cyfa_bwd_f32_short.h"
 
 namespace cyfa {
 
@@ -491,12 +492,27 @@ __global__ __launch_bounds__(128, 1) void f32_grad_kernel(BwdParams p, F32Ws w) 
     }
 }
 
-// workgroups per head of the readout kernel: one round over the compute units, each
-// with the same number of chunk pairs
-int readout_wgs(int B, int H, int nc, int *per) {
-    const int np = B * ((nc + 1) / 2);
-    int n = (256 + H - 1) / H;
+// Short calls: up to kShortChunks 64-token chunks, or one chunk per sequence, with d_k and d_v
+// at most 128.  The kernels of this file take about 200 us (d = 64) or 240 us (128) however few
+// the tokens, those of cyfa_bwd_f32_short.h 80 .. 100 and 100 .. 125; at 128 chunks (B 4, T 200,
+// H 8) 231 against 115 us and 274 against 154, at 384 (B 8, T 130, H 16) 265 against 221 and
+// 307 against 293.  Beyond, the workgroup of four waves per 32 tokens fetches the matrices too
+// often: d = 128, 512 chunks 338 against 359 us, 2048 1242 against 1310.  A sequence of one
+// chunk leaves half of a chunk pair idle: 512 sequences of 64 tokens 457 against 382 us (d = 128)
+// and 379 against 271 (64), 2048 of 16 tokens 1652 against 931 and 1398 against 682.
+constexpr int kShortChunks = 384;
+bool short_call(const BwdParams &p) {
+    return p.dk <= 128 && p.dv <= 128 && (p.nc == 1 || (long long)p.B * p.H * p.nc <= kShortChunks);
+}
+
+// Workgroups per head of the readout kernel: one round over the compute units, each with the
+// same number of chunk pairs; in a short call two rounds of the 32-token tiles' workgroups.
+int readout_wgs(const BwdParams &p, int *per) {
+    const bool tiles = short_call(p);
+    const int np = tiles ? p.B * ((p.T + 31) / 32) : p.B * ((p.nc + 1) / 2);
+    int n = ((tiles ? 512 : 256) + p.H - 1) / p.H;
     if (n > np) n = np;
+    if (tiles) return n;
     *per = (np + n - 1) / n;
     return (np + *per - 1) / *per;
 }
@@ -506,13 +522,22 @@ hipError_t launch_typed(const BwdParams &p, const F32Ws &w, hipStream_t s) {
     const int BH = p.B * p.H;
     launch_front(p, w, s);
     launch_states<DK, DV, Tin, false>(p, w, s);
-    int per = 1, nu = 0;
-    if (p.nc > 0) {
-        nu = readout_wgs(p.B, p.H, p.nc, &per);
-        hipLaunchKernelGGL((f32_readout_kernel<DK, DV, Tin>), dim3(p.H, nu), dim3(256), 0, s, p, w, per);
+    int per = 1;
+    const int nu = p.nc > 0 ? readout_wgs(p, &per) : 0;
+    const bool few = p.nc > 0 && short_call(p);
+    if constexpr (DK <= 128) {
+        if (few)
+            hipLaunchKernelGGL((f32_readout_short_kernel<DK, DV, Tin>), dim3(p.H, nu), dim3(256), 0, s, p, w);
     }
+    if (p.nc > 0 && !few)
+        hipLaunchKernelGGL((f32_readout_kernel<DK, DV, Tin>), dim3(p.H, nu), dim3(256), 0, s, p, w, per);
     launch_states<DK, DV, Tin, true>(p, w, s);
-    if (p.nc > 0) hipLaunchKernelGGL((f32_grad_kernel<DK, DV, Tin>), dim3(p.nc * BH), dim3(128), 0, s, p, w);
+    if constexpr (DK <= 128) {
+        if (few)
+            hipLaunchKernelGGL((f32_grad_short_kernel<DK, DV, Tin>), dim3(p.nc * BH), dim3(512), 0, s, p, w);
+    }
+    if (p.nc > 0 && !few)
+        hipLaunchKernelGGL((f32_grad_kernel<DK, DV, Tin>), dim3(p.nc * BH), dim3(128), 0, s, p, w);
     BwdParams tail = p;
     tail.groups = 1;                // dMp is [nu][H][128][128]
     return launch_bwd_tail(tail, nu, s);
@@ -530,6 +555,8 @@ hipError_t launch_dtype(const BwdParams &p, const F32Ws &w, hipStream_t s) {
 static size_t need_bytes(int B, int T, int H, int dk, int dv) {
     const size_t BH = (size_t)B * H, nc = ((size_t)T + kTC - 1) / kTC, Tpad = nc * kTC;
     int per = 1;
+    BwdParams p{};
+    p.B = B; p.T = T; p.H = H; p.dk = dk; p.dv = dv; p.nc = (int)nc;
     size_t n = align_up(2 * readout_f32_bytes(H));
     n += align_up(BH * nc * 8);
     n += align_up(BH * Tpad * kR * 4);
@@ -539,7 +566,7 @@ static size_t need_bytes(int B, int T, int H, int dk, int dv) {
     n += 2 * (align_up(BH * nc * kR * dk * 4) + align_up(BH * nc * kR * dv * 4));
     n += 2 * align_up(BH * Tpad * kR * 4);
     n += 3 * align_up(BH * Tpad * 4);
-    if (nc > 0) n += align_up((size_t)readout_wgs(B, H, (int)nc, &per) * H * kR * kR * 4);
+    if (nc > 0) n += align_up((size_t)readout_wgs(p, &per) * H * kR * kR * 4);
     n += align_up(BH * kBwdFinParts * 8);
     return n;
 }
@@ -580,7 +607,7 @@ hipError_t launch_bwd_f32(BwdParams p, void *ws, hipStream_t s) {
     p.dlam = take(BH * Tpad * 4);
     p.dG = take(BH * Tpad * 4);
     int per = 1;
-    if (nc > 0) p.dMp = take((size_t)readout_wgs(p.B, p.H, p.nc, &per) * p.H * kR * kR * 4);
+    if (nc > 0) p.dMp = take((size_t)readout_wgs(p, &per) * p.H * kR * kR * 4);
     p.fin = reinterpret_cast<double *>(take(BH * kBwdFinParts * 8));
     if (p.dk == 64 && p.dv == 64) return launch_dtype<64, 64>(p, w, s);
     if (p.dk == 64 && p.dv == 128) return launch_dtype<64, 128>(p, w, s);

@@ -340,13 +340,13 @@ template <int DK, int DV, typename Tin, bool ADJ, bool WALK>
 __global__ __launch_bounds__(256, 4) void f32_states_kernel(BwdParams p, F32Ws w) {
     __shared__ __attribute__((aligned(16))) float lds[kTC * kLS + kTC + 4 * kLdsTile];
     const int y = blockIdx.y;
-    if (WALK && !ADJ) clock_to_caller(w, blockIdx.x);
     if (y < DK / 64)
         state_columns<DK, Tin, ADJ, WALK>(p, w, ADJ ? p.q : p.k, ADJ ? p.dP : w.cs, ADJ ? w.DKe : w.Kst,
                                           ADJ ? p.dK_T : p.K0, p.dK_T, ADJ ? p.gK0 : w.Ko, y, lds);
     else
         state_columns<DV, Tin, ADJ, WALK>(p, w, ADJ ? p.dout : p.v, ADJ ? p.U : w.cs, ADJ ? w.DVe : w.Vst,
                                           ADJ ? p.dV_T : p.V0, p.dV_T, ADJ ? p.gV0 : w.Vo, y - DK / 64, lds);
+    if (WALK && !ADJ) clock_to_caller(w, blockIdx.x);
 }
 
 // Combines the chunks' own contributions in place, element by element: slot c becomes
@@ -360,7 +360,6 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
     const int bh = blockIdx.x, tid = threadIdx.x, m = p.m, nc = p.nc;
     const float *ge = w.gend + (size_t)bh * nc;
     double fin = 0.0;
-    if (!ADJ) clock_to_caller(w, bh);
     auto run = [&](int D, float *slots, const float *ext, const float *fext, float *gext) {
         const size_t st = (size_t)kR * D / 4;
         for (int e = (blockIdx.y % kHalf) * 256 + tid; e < kR * D / 4; e += 256 * kHalf) {
@@ -407,12 +406,35 @@ __global__ __launch_bounds__(256) void f32_scan_kernel(BwdParams p, F32Ws w) {
         run(DK, ADJ ? w.DKe : w.Kst, ADJ ? p.dK_T : p.K0, p.dK_T, ADJ ? p.gK0 : w.Ko);
     else
         run(DV, ADJ ? w.DVe : w.Vst, ADJ ? p.dV_T : p.V0, p.dV_T, ADJ ? p.gV0 : w.Vo);
+    if (!ADJ) clock_to_caller(w, bh);
     if (ADJ || !p.fin) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) fin += __shfl_xor(fin, o);
     if ((tid & 63) == 0) red[tid >> 6] = fin;
     __syncthreads();
     if (tid == 0) p.fin[(size_t)bh * kBwdFinParts + blockIdx.y] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// U(sign lambda) of one block of basis rows; t = its phases
+__device__ __forceinline__ f32x16 rotate_block(const f32x16 &x, const f32x16 &t, float sign, float mul) {
+    f32x16 y;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        const float c = t[r], s = sign * t[r + 1];
+        y[r] = mul * (c * x[r] - s * x[r + 1]);
+        y[r + 1] = mul * (s * x[r] + c * x[r + 1]);
+    }
+    return y;
+}
+
+// block row w of a 4 x 4-block matrix times four operand blocks in LDS, in two sums
+__device__ __forceinline__ f32x16 row_product(const float *Mat, int w, const float *x, int lane4) {
+    f32x16 a[4], s[2] = {};
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) a[kb] = ld_block(Mat + (4 * w + kb) * 1024 + lane4);
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) mma_step(s[kb >> 1], a[kb], ld_block(x + kb * 1024 + lane4));
+    return s[0] + s[1];
 }
 
 template <int DK, int DV, typename Tin, bool ADJ>

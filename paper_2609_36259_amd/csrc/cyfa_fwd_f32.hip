@@ -20,28 +20,6 @@ namespace cyfa {
 
 namespace {
 
-// U(sign lambda) of one block of basis rows; t = its phases
-__device__ __forceinline__ f32x16 rotate_block(const f32x16 &x, const f32x16 &t, float sign, float mul) {
-    f32x16 y;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-        const float c = t[r], s = sign * t[r + 1];
-        y[r] = mul * (c * x[r] - s * x[r + 1]);
-        y[r + 1] = mul * (s * x[r] + c * x[r + 1]);
-    }
-    return y;
-}
-
-// block row w of a 4 x 4-block matrix times four operand blocks in LDS, in two sums
-__device__ __forceinline__ f32x16 row_product(const float *Mat, int w, const float *x, int lane4) {
-    f32x16 a[4], s[2] = {};
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) a[kb] = ld_block(Mat + (4 * w + kb) * 1024 + lane4);
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) mma_step(s[kb >> 1], a[kb], ld_block(x + kb * 1024 + lane4));
-    return s[0] + s[1];
-}
-
 template <int DK, int DV, typename Tin>
 __global__ __launch_bounds__(256, 2) void f32_forward_kernel(BwdParams p, F32Ws w, void *out, float *logits) {
     __shared__ __attribute__((aligned(16))) float xs[4096], ws[4096], part[4096], tiles[4 * kLdsTile];

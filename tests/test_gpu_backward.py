@@ -226,3 +226,69 @@ def test_f32_strong_decay():
     x["log_alpha"][:, 64:110] = -40.0
     e = _extras(x, 13)
     _compare(_run(x, e), _oracle(x, e), TOL_F32)
+
+
+def _sampled(x, e, lens, g, b, h, tol, skip=()):
+    """One sequence of a batch against the oracle run on that sequence alone."""
+    sl = lambda a: None if a is None else np.ascontiguousarray(a[b:b + 1, :, h:h + 1])  # noqa: E731
+    ss = lambda a: None if a is None else np.ascontiguousarray(a[b:b + 1, h:h + 1])     # noqa: E731
+    y = dict(x, q=sl(x["q"]), k=sl(x["k"]), v=sl(x["v"]), delta=sl(x["delta"]),
+             log_alpha=sl(x["log_alpha"]), beta=sl(x["beta"]), R=x["R"][h:h + 1])
+    f = dict({n: ss(e[n]) for n in e if n != "do"}, do=sl(e["do"]))
+    ref = _oracle(y, f, lens=None if lens is None else lens[b:b + 1])
+    pick = {k: (v[b:b + 1, :, h:h + 1] if k in ("dq", "dk", "dv", "d_delta", "d_log_alpha", "d_beta")
+                else v[b:b + 1, h:h + 1] if k in ("d_K0", "d_V0", "d_clock0") else v[h:h + 1])
+            for k, v in g.items() if v is not None}
+    _compare(pick, ref, tol, skip=skip)
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv,m,dtype,lens", [
+    (1, 129, 130, 64, 64, 127, "f32", None),       # 390 chunks; the last pair of a sequence has one
+    (1, 128, 193, 64, 128, 31, "f32", None),
+    (2, 129, 65, 128, 64, 127, "f32", (129, 66)),
+    (2, 65, 97, 128, 128, 127, "f32", (65, 1)),      # (0: the clock gradient is 0, the oracle's its rounding)
+    (1, 129, 130, 64, 64, 127, "bf16", None),
+])
+def test_long_call_kernels(B, T, H, dk, dv, m, dtype, lens):
+    """Calls just over 384 chunks, at chunk-pair edges: first, middle and last sequence (with
+    one batch entry d_R is the sequence's own)."""
+    x = make_forward_inputs(B, T, H, dk, dv, seed=140 + T, dtype=dtype, m=m)
+    e = _extras(x, 14)
+    lens = None if lens is None else np.array(lens, np.int32)
+    g = _run(x, e, lens=lens)
+    for b, h in ((0, 0), (0, H // 2), (B - 1, H - 1)):
+        _sampled(x, e, lens, g, b, h, TOL_F32 if dtype == "f32" else TOL_BF16, skip=() if B == 1 else ("d_R",))
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv,m,dtype", [
+    (1, 32, 2, 64, 128, 127, "f32"), (3, 33, 1, 128, 64, 3, "f32"), (2, 96, 2, 128, 128, 65, "f32"),
+    (1, 97, 1, 64, 64, 127, "bf16"), (1, 200, 96, 64, 64, 127, "f32"),     # 384 chunks: the line
+])
+def test_short_call_tile_edges(B, T, H, dk, dv, m, dtype):
+    """32-token tile edges of the short calls' kernels, their head dimensions and small m."""
+    x = make_forward_inputs(B, T, H, dk, dv, seed=150 + T, dtype=dtype, m=m)
+    e = _extras(x, 15)
+    g = _run(x, e)
+    for b, h in {(0, 0), (B - 1, H - 1)}:
+        _sampled(x, e, None, g, b, h, TOL_F32 if dtype == "f32" else TOL_BF16, skip=() if B == 1 else ("d_R",))
+
+
+def test_short_call_many_sequences_share_workgroups():
+    """600 sequences of up to two tiles: more tiles than the readout kernel has workgroups, whose
+    dM then sums several tiles, absent ones among them.  Against the same sequences 150 at a
+    time, one tile per workgroup: the token gradients bit for bit, d_R to 1e-5 (fp32 sums of
+    the same terms in another order)."""
+    cyfa = _cyfa()
+    B, T, H, d = 600, 40, 1, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(16)
+    q, k, v, d_o = (torch.randn((B, T, H, d), device="cuda", generator=g) for _ in range(4))
+    la, delta = -torch.rand((B, T, H), device="cuda", generator=g), torch.rand((B, T, H), device="cuda", generator=g)
+    beta, R = torch.rand((B, T, H), device="cuda", generator=g), torch.eye(127, device="cuda")[None].contiguous()
+    lens = torch.tensor([(40, 33, 32, 5, 0)[b % 5] for b in range(B)], dtype=torch.int32, device="cuda")
+    run = lambda s: cyfa.backward(q[s], k[s], v[s], delta[s], la[s], beta[s], R, d_o=d_o[s], lens=lens[s])  # noqa: E731
+    full, parts = run(slice(None)), [run(slice(i, i + 150)) for i in range(0, B, 150)]
+    for name in ("dq", "dk", "dv", "d_delta", "d_log_alpha", "d_beta"):
+        assert torch.equal(full[name], torch.cat([x[name] for x in parts])), name
+    ref = sum(x["d_R"] for x in parts)
+    assert (full["d_R"] - ref).abs().max() <= 1e-5 * ref.abs().max()

@@ -116,7 +116,13 @@ typedef struct {
     int32_t kernel;  /* cyfa_kernel */
 } cyfa_fwd_desc;
 
-/* Bytes of device workspace cyfa_forward needs for `desc` (host-only query). */
+/*
+ * Bytes of device workspace cyfa_forward needs for `desc` (host-only query).  The fp32
+ * forward on the matrix instructions keeps both states entering every 64-token chunk
+ * (B H ceil(T/64) 128 (d_k + d_v) floats) and a 128-float row of phases per token and head:
+ * 0.68 GB at B=4, T=4096, H=16, d=128.  With segments = 1 (the vector-ALU kernel) it is
+ * the readout matrices alone, 64 KB per head for m <= 127.
+ */
 cyfa_status cyfa_forward_workspace_size(const cyfa_fwd_desc *desc, size_t *bytes);
 
 /*
@@ -139,7 +145,9 @@ cyfa_status cyfa_forward_workspace_size(const cyfa_fwd_desc *desc, size_t *bytes
  *   K0, V0      [B, H, 128, d_k] / [B, H, 128, d_v] float initial absolute-clock
  *               states; NULL means zero
  *   clock0      [B, H] double initial clock lambda_0; NULL means 0
- *   o           [B, T, H, d_v] dtype output (required)
+ *   o           [B, T, H, d_v] dtype output (required).  In the fp32 forward and in the
+ *               vector-ALU kernel a NaN or infinity in any input of a token reaches no
+ *               earlier token's output
  *   K_out,V_out [B, H, 128, d] float final states, or NULL to skip; may alias
  *               K0 / V0 (resume in place); must not alias any other argument
  *   clock_out   [B, H] double final clock reduced mod m, or NULL; may alias clock0
@@ -255,9 +263,10 @@ cyfa_status cyfa_backward_workspace_size(const cyfa_fwd_desc *desc, size_t *byte
  * are written, not accumulated.  Outputs must not alias inputs or each other.
  * workspace  at least cyfa_backward_workspace_size bytes, 256-byte aligned.
  * The fp32 backward computes in fp32 (on the fp32 matrix instructions); the
- * matrix-core one multiplies bf16
- * operands with fp32 accumulation (states, adjoints and reductions in fp32).  bf16
- * gradients are rounded to nearest even.
+ * matrix-core one multiplies bf16 operands with fp32 accumulation (states, adjoints
+ * and reductions in fp32).  bf16 gradients are rounded to nearest even.
+ * A NaN or infinity in any input of a token may make every gradient of its sequence
+ * (and d_R of its head) not finite.
  */
 cyfa_status cyfa_backward(const cyfa_fwd_desc *desc,
                           const void *q, const void *k, const void *v,

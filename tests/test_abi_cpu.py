@@ -59,6 +59,19 @@ def test_descriptor_validation(field, value, status):
         _ws(d)
 
 
+@pytest.mark.parametrize("B,T,H,dk,dv,dtype", [(4, 4096, 16, 128, 128, cyfa.F32), (1, 65, 3, 64, 256, cyfa.BF16),
+                                               (2, 0, 1, 64, 64, cyfa.F32)])
+def test_fp32_forward_workspace_is_the_stated_one(B, T, H, dk, dv, dtype):
+    """What the header states (states per 64-token chunk, a row of phases per token), with
+    the readout matrices and the per-token scalars, each piece 256-byte aligned."""
+    BH, nc = B * H, (T + 63) // 64
+    rows = BH * nc * 64
+    al = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    want = (al(2 * H * 65536) + al(BH * nc * 8) + al(BH * 8) + al(rows * 512) + al(rows * 8) + al(rows * 12)
+            + al(BH * nc * 4) + al(BH * nc * 512 * dk) + al(BH * nc * 512 * dv))
+    assert _ws(cyfa.forward_desc(B, T, H, dk, dv, dtype=dtype, kernel=cyfa.KERNEL_VALU)) == want
+
+
 def test_status_codes():
     lib = cyfa.load()
     n = ctypes.c_size_t(0)

@@ -38,7 +38,7 @@ def test_workspace_sizes_and_kernel_selection():
     d = cyfa.forward_desc(1, 256, 2, 64, 64, dtype=cyfa.F32, segments=1)
     assert _ws(d) == 2 * 128 * 128 * 4            # one chunk group: the readout matrices only
     d = cyfa.forward_desc(1, 256, 2, 64, 64, dtype=cyfa.F32)
-    assert _ws(d) > 2 * 128 * 128 * 4             # automatic chunk groups: their entering states
+    assert _ws(d) > 2 * 128 * 128 * 4             # the fp32 matrix-instruction forward: its chunks' states
     d = cyfa.forward_desc(1, 256, 2, 256, 64, dtype=cyfa.F32, segments=4)
     with pytest.raises(cyfa.CyfaError):
         _ws(d)                                    # groups need d <= 128
@@ -223,7 +223,7 @@ def _call_backward(desc, ptrs, ws=0, ws_bytes=0):
 def test_backward_workspace_and_descriptor_checks():
     d = cyfa.forward_desc(4, 4096, 16, 128, 128, dtype=cyfa.BF16, kernel=cyfa.KERNEL_VALU)
     n = cyfa.backward_workspace_size(d)
-    # vector-ALU: entering and adjoint states per 16-token chunk dominate, ~4.3 GB at this shape
+    # fp32: room for entering and adjoint states per 16-token chunk, ~4.3 GB at this shape
     assert 4.0e9 < n < 5.0e9
     # matrix-core (the automatic choice here): u and dp per token in bf16 (2 x 67 MB), the
     # forward and adjoint states per chunk group (2 x 34 MB), the groups' dM (17 MB)

@@ -1,4 +1,4 @@
-"""GPU parity of the vector-ALU backward (cyfa_backward, kernel VALU) against the
+"""GPU parity of the fp32 backward (cyfa_backward, kernel VALU) against the
 backward oracle (head dims 64 and 128 in any combination, and both 256).
 
 Every gradient tensor is compared element by element with the oracle's float64
@@ -51,7 +51,7 @@ def _extras(x, seed, init=True, final=True):
 
 
 def _run(x, e, lens=None, groups=0):
-    """The vector-ALU backward (fp32 arithmetic); the matrix-core one has its own file."""
+    """The fp32 backward; the bf16 matrix-core one has its own file."""
     cyfa = _cyfa()
     t = upload(x)
     dt = t["q"].dtype

@@ -7,7 +7,7 @@ final-state adjoints; error per tensor max |x - y| / max |y|, bar 2e-2 (bf16
 operands, fp32 accumulation).  Cases: several chunks with a ragged tail, m = 7
 and 127, initial and final states, chunk groups, ragged lengths (padding rows
 written as 0), absent gates / states, the identity readout, a peaky readout,
-T = 0, the vector-ALU backward on the same inputs, and one full sequence of the
+T = 0, the fp32 backward on the same inputs, and one full sequence of the
 1.4B-scale workload in the benchmark's launch configuration.
 
 d_delta and d_log_alpha are reverse cumulative sums of per-token terms (the

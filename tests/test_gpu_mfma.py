@@ -63,7 +63,7 @@ def test_small_full_parity_and_segment_invariance(chunk, segments):
 
 def test_chunk_length_changes_only_rounding():
     """Chunk 32 and 64 on the matrix cores (64 runs as two 32-token chunks, so the
-    two agree bit for bit), and the vector-ALU kernel at chunk 8 and 16."""
+    two agree bit for bit), and the fp32 forward asked for chunk 8 and 16."""
     x = make_forward_inputs(2, 64 * 5 + 17, 2, 128, 128, seed=49, dtype="bf16")
     t = upload(x)
     a = _fwd(x, t, chunk=32, return_state=True)

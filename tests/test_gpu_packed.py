@@ -4,8 +4,8 @@ Every sequence of the packed batch is compared with the oracle run on that
 sequence alone (outputs, slot logits, final states and clocks), and the whole
 call with cyfa_forward_lens on the same sequences padded to T rows, which runs
 the same kernels: outputs, logits and states must be bit-identical.  Both the
-matrix-core (bf16) and the vector-ALU (fp32) forward, with several segments /
-chunk groups, empty and one-token sequences, and initial states.
+matrix-core (bf16) and the fp32 forwards (fp32 matrix instructions; vector ALU with one
+segment), with several segments, empty and one-token sequences, and initial states.
 """
 import numpy as np
 import pytest

@@ -1,4 +1,5 @@
-"""GPU parity of the vector-ALU forward kernel and of the decode step against the oracle."""
+"""GPU parity of the fp32-arithmetic forwards (fp32 matrix instructions; vector ALU for m > 127
+and with one segment) and of the decode step against the oracle."""
 import numpy as np
 import pytest
 import oracle
@@ -306,8 +307,8 @@ def oracle_forward_decode(x, pairs):
 
 @pytest.mark.parametrize("segments,chunk", [(1, 16), (3, 16), (5, 8), (0, 16)])
 def test_valu_chunk_groups(segments, chunk):
-    """The vector-ALU forward over chunk groups (each group's entering state from a
-    pre-pass over the earlier groups) against the oracle, with an initial state."""
+    """The fp32-arithmetic forward against the oracle, with an initial state: the vector-ALU
+    kernel with one segment, the fp32 matrix instructions with any other segment count."""
     cyfa = _cyfa()
     x = make_forward_inputs(2, 16 * 9 + 5, 2, 64, 128, seed=26, dtype="f32")
     t = upload(x)
@@ -339,9 +340,8 @@ def test_valu_chunk_groups(segments, chunk):
 
 
 def test_valu_full_size_f32_chunk_groups():
-    """The vector-ALU forward at the 1.4B layer shape (B4 T4096 H16 d128) with fp32
-    inputs, in its automatic chunk-group split (the fp32 path of that shape);
-    eight (b, h) sequences, first, last and interior, compared over all tokens."""
+    """The fp32 forward (fp32 matrix instructions) at the 1.4B layer shape (B4 T4096 H16
+    d128) with fp32 inputs; eight (b, h) sequences, first, last and interior, compared over all tokens."""
     from paper_2609_36259_amd.inputs import FWD_1P4B
     cyfa = _cyfa()
     w = FWD_1P4B
@@ -361,6 +361,26 @@ def test_valu_full_size_f32_chunk_groups():
     print("errors", {k: f"{v:.2e}" for k, v in errs.items()}, flush=True)
     for k, v in errs.items():
         assert v <= (1e-9 if k == "clock" else TOL_F32), (k, v)
+
+
+@pytest.mark.parametrize("dk,dv,m,chunk,dtype", [
+    (64, 64, 127, 8, "f32"), (128, 128, 7, 8, "bf16"), (256, 256, 127, 16, "f32"), (256, 64, 127, 8, "f32"),
+    (64, 256, 31, 16, "bf16"), (128, 64, 255, 8, "f32"),
+])
+def test_valu_one_segment(dk, dv, m, chunk, dtype):
+    """The vector-ALU forward (one segment per sequence): both chunk lengths, 256-channel heads
+    and 256 storage rows, ragged tail, resumed in place from the first call's state."""
+    cyfa = _cyfa()
+    T1, T = 21, 75
+    x = make_forward_inputs(2, T, 2, dk, dv, seed=330 + dk, dtype=dtype, m=m)
+    t = upload(x)
+    cut = lambda lo, hi: [v[:, lo:hi].contiguous() if n != "R" else v for n, v in t.items()]  # noqa: E731
+    kw = dict(scale=x["scale"], m=m, kernel=cyfa.KERNEL_VALU, segments=1, chunk=chunk, return_logits=True)
+    a = cyfa.forward(*cut(0, T1), return_state=True, **kw)
+    K, V, clock = a["K"], a["V"], a["clock"]
+    b = cyfa.forward(*cut(T1, T), K0=K, V0=V, clock0=clock, K_out=K, V_out=V, clock_out=clock, **kw)
+    res = dict(o=torch.cat([a["o"], b["o"]], 1), logits=torch.cat([a["logits"], b["logits"]], 1), K=K, V=V, clock=clock)
+    _check_full(x, res, TOL_F32 if dtype == "f32" else TOL_BF16)
 
 
 @pytest.mark.parametrize("B,T,H,dk,dv,dtype", [

@@ -85,7 +85,11 @@ __device__ __forceinline__ void chunk_tables(const BwdParams &p, const F32Ws &w,
         const bool live = t < Tb;
         const size_t si = (g0 + t) * p.H + h;
         const double dl = live ? (double)p.delta[si] : 0.0;
-        const double la = live && p.log_alpha ? (double)p.log_alpha[si] * 1.4426950408889634 : 0.0;
+        // A decay below 2^-1024 is 0 in fp32 with any token before it, so the bound changes no
+        // result but keeps the chunk's prefix sums from absorbing the later tokens' decays after
+        // a reset (log alpha = -1e38, -inf).
+        double la = live && p.log_alpha ? (double)p.log_alpha[si] * 1.4426950408889634 : 0.0;
+        la = la < -1024.0 ? -1024.0 : la;       // (a NaN stays)
         const float be = live ? (p.beta ? p.beta[si] : 1.f) : 0.f;
         const double lam = reduce_clock(lam0 + mfma::wave_incl_scan(dl), m);
         const double G = mfma::wave_incl_scan(la), GC = mfma::lane63(G);

@@ -228,6 +228,16 @@ def test_f32_strong_decay():
     _compare(_run(x, e), _oracle(x, e), TOL_F32)
 
 
+@pytest.mark.parametrize("H", [2, 200])
+def test_f32_hard_resets(H):
+    """Forget gates of the type's lowest value, two in one 64-token chunk (short and long calls'
+    kernels): the tokens after a reset keep their own decays."""
+    x = make_forward_inputs(1, 100, H, 64, 64, seed=98, dtype="f32")
+    x["log_alpha"][:, [10, 30, 70]] = np.finfo(np.float32).min
+    e = _extras(x, 17)
+    _sampled(x, e, None, _run(x, e), 0, H - 1, TOL_F32)
+
+
 def _sampled(x, e, lens, g, b, h, tol, skip=()):
     """One sequence of a batch against the oracle run on that sequence alone."""
     sl = lambda a: None if a is None else np.ascontiguousarray(a[b:b + 1, :, h:h + 1])  # noqa: E731

@@ -488,7 +488,7 @@ def test_f32_forward_nan_stays_causal():
 def test_f32_forward_nonfinite_gates_stay_causal(name):
     """A NaN or infinity in a gate of one token, inside and at the edges of the 32-token
     tiles and 64-token chunks, reaches no earlier token, and the token itself is not finite
-    (alpha = 0 aside, whose decay from the token to itself is a matter of definition)."""
+    (log alpha = -inf is alpha = 0, no fault)."""
     cyfa = _cyfa()
     x = make_forward_inputs(1, 96, 1, 64, 64, seed=313, dtype="f32")
     t = upload(x)
@@ -501,8 +501,19 @@ def test_f32_forward_nonfinite_gates_stay_causal(name):
             bad[0, at, 0] = value
             o = run(**{name: bad})
             assert (o[:, :at] - clean[:, :at]).abs().max() < 1e-5, (value, at)
-            if not (name == "log_alpha" and value < 0):
+            if name == "log_alpha" and value < 0:
+                assert torch.isfinite(o).all(), at
+            else:
                 assert not torch.isfinite(o[0, at, 0]).any(), (value, at)
+
+
+@pytest.mark.parametrize("value", [-1e6, float(np.finfo(np.float32).min), float("-inf")])
+def test_f32_forward_hard_resets(value):
+    """Forget gates that erase the state (the type's lowest value, alpha = 0), two of them in one
+    64-token chunk: the tokens after a reset keep their own decays."""
+    x = make_forward_inputs(1, 150, 2, 64, 64, seed=317, dtype="f32")
+    x["log_alpha"][:, [10, 30, 64, 127]] = value
+    _check_full(x, _fwd(x, upload(x), return_state=True, return_logits=True), TOL_F32)
 
 
 @pytest.mark.parametrize("m", [3, 65, 127])

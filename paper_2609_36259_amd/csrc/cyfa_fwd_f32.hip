@@ -10,9 +10,9 @@
 // tokens, in tiles with the tokens on the lanes (cyfa_tile_f32.h), and reads the other
 // waves' rows from LDS as operand blocks.  The split over the four waves is for the small
 // calls this path serves: a tile's chain of 72 (d = 64) steps of 16 instructions, 1024
-// cycles each, becomes 24 steps and six barriers.  B 1, T 256, H 2, d 64 (fp32): 186 us
-// with the vector-ALU chunk kernel (147 us of it that kernel), 41 us now (this kernel 25,
-// the tables 7.5, the states 9.6); bound by each tile's chain of products and barriers.
+// cycles each, becomes 24 steps and six barriers.  B 1, T 256, H 2, d 64 (fp32): 187 us
+// with the vector-ALU chunk kernel (147 us of it that kernel), 38 us now (this kernel 22.8,
+// the tables 8.9, the states 5.1 and their scan 3.4); bound by each tile's chain of products and barriers.
 #include "cyfa_f32_common.h"
 #include "cyfa_rows.h"
 

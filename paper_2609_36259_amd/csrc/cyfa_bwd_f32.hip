@@ -495,12 +495,14 @@ __global__ __launch_bounds__(128, 1) void f32_grad_kernel(BwdParams p, F32Ws w) 
 // Short calls: up to kShortChunks 64-token chunks, or one chunk per sequence, with d_k and d_v
 // at most 128.  The kernels of this file take about 200 us (d = 64) or 240 us (128) however few
 // the tokens, those of cyfa_bwd_f32_short.h 80 .. 100 and 100 .. 125; at 128 chunks (B 4, T 200,
-// H 8) 231 against 115 us and 274 against 154, at 384 (B 8, T 130, H 16) 265 against 221 and
-// 307 against 293.  Beyond, the workgroup of four waves per 32 tokens fetches the matrices too
-// often: d = 128, 512 chunks 338 against 359 us, 2048 1242 against 1310.  A sequence of one
-// chunk leaves half of a chunk pair idle: 512 sequences of 64 tokens 457 against 382 us (d = 128)
-// and 379 against 271 (64), 2048 of 16 tokens 1652 against 931 and 1398 against 682.
-constexpr int kShortChunks = 384;
+// H 8) 231 against 115 us and 274 against 154, at 256 (B 8, T 100, H 16) 246 against 156 and 285
+// against 201, or with one head (B 64, T 200) 266 against 210 and 298 against 248.  Beyond, four
+// waves per 32 tokens fetch the matrices too often and leave dR too many partial sums per head:
+// at 384 chunks 307 against 293 us with 16 heads (d = 128, B 8, T 130), but 334 against 370 with
+// one (B 64, T 380); at 512 338 against 359.  A sequence of one chunk leaves half of a
+// chunk pair idle: 512 sequences of 64 tokens 457 against 382 us (d = 128) and 379 against 271
+// (64), 2048 of 16 tokens 1652 against 931 and 1398 against 682.
+constexpr int kShortChunks = 256;
 bool short_call(const BwdParams &p) {
     return p.dk <= 128 && p.dv <= 128 && (p.nc == 1 || (long long)p.B * p.H * p.nc <= kShortChunks);
 }
